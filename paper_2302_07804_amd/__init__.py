@@ -15,7 +15,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
 LIB_PATH = os.path.join(_HERE, "libhenry.so")
 _SOURCES = [os.path.join(_HERE, "csrc", f) for f in ("henry_api.hip", "henry_solve512.hip", "henry_mlmc_plan.cpp")]
-_DEPS = [os.path.join(_HERE, "csrc", f) for f in ("henry_device.hpp", "henry_mlmc.hpp", "henry_adjoint.hpp")] + \
+_DEPS = [os.path.join(_HERE, "csrc", f) for f in ("henry_device.hpp", "henry_wave.hpp", "henry_mlmc.hpp", "henry_adjoint.hpp")] + \
     [os.path.join(_ROOT, "include", "henry.h")]
 
 HENRY_OK, HENRY_EINVAL, HENRY_ENOMEM, HENRY_EHIP, HENRY_ENOCONV, HENRY_ENONFINITE = 0, -1, -2, -3, -4, -5

@@ -231,6 +231,7 @@ struct Solve {
     double *p, *c, *cn, *phi, *K, *pp, *tx, *ty, *wx, *wy, *isc, *c2, *p2, *c3, *p3, *c4, *p4, *scratch;
     Level<T> lv[kMaxLevels];
     Level<T> hg;  // the global-memory arrays of level lb
+    T* wave;      // LDS of the levels wavefront 0 runs (henry_wave.hpp)
     double *rout_p, *rout_c;  // residual outputs (henry_residual_kernel)
 };
 
@@ -242,6 +243,52 @@ __host__ __device__ inline bool level_in_lds(int l, int cells, int lds_cells, in
     return cells <= lds_cells || (l >= 1 && cells <= lds_block_cells);
 }
 
+// One wave level of NX x NX/2 cells: x with a halo of one cell around it
+// (pressure: two colours of H cells per row, each with its own halo;
+// transport: rows of NX cells from column 2 on), the residual that the
+// restriction reads (red cells, or even rows), and for the levels below the
+// first the coefficients and right-hand side.  Levels lie one after another
+// from the coarsest up, so their places do not depend on which is first.
+constexpr int ilog2(int v) { return v > 1 ? 1 + ilog2(v / 2) : 0; }
+constexpr int round4(int v) { return (v + 3) & ~3; }
+template <int NX>
+struct WaveDim {
+    static constexpr int NY = NX / 2, H = NX / 2, N = NX * NY;
+    static constexpr int CS = H + 2;       // colour stride (pressure)
+    static constexpr int RS = NX + 4;      // row stride of x
+    static constexpr int kX = (NY + 2) * RS;
+    static constexpr int kR = (NY + 2) * CS;  // red cells; the even rows (NY/2 + 1) * RS take no more
+    static constexpr int kXR = round4(kX + kR);
+    static constexpr int kCoef = round4(6 * N + 4 * NY);
+    static constexpr int base() {
+        if constexpr (NX == 2) return 0;
+        else return WaveDim<NX / 2>::base() + WaveDim<NX / 2>::kXR + WaveDim<NX / 2>::kCoef;
+    }
+};
+// Elements of the wave region below a first level of nx columns.
+__host__ __device__ inline int wave_region_elems(int nx) {
+    switch (nx) {
+        case 2: return WaveDim<2>::base() + WaveDim<2>::kXR;
+        case 4: return WaveDim<4>::base() + WaveDim<4>::kXR;
+        case 8: return WaveDim<8>::base() + WaveDim<8>::kXR;
+        case 16: return WaveDim<16>::base() + WaveDim<16>::kXR;
+        default: return WaveDim<32>::base() + WaveDim<32>::kXR;
+    }
+}
+
+// The first level that wavefront 0 runs keeps its arrays but r in LDS (the
+// rest of the workgroup, or the cluster, writes its coefficients and
+// right-hand side and reads its x); what it and the coarser levels need
+// besides lives in the wave region after them (henry_wave.hpp).
+template <typename T>
+__host__ __device__ inline int64_t wave_top_bytes(int nx, int ny) {
+    return align256((int64_t)((kLevelArrays - 1) * nx * ny + kRowArrays * ny) * (int64_t)sizeof(T));
+}
+template <typename T>
+__host__ __device__ inline int64_t wave_region_bytes(int nx) {
+    return align256((int64_t)wave_region_elems(nx) * (int64_t)sizeof(T));
+}
+
 // Dynamic LDS bytes for the LDS levels of an nx x ny hierarchy.
 template <typename T>
 __host__ __device__ inline int64_t lds_level_bytes(int nx, int ny, int lds_cells, int lds_block_cells) {
@@ -249,6 +296,7 @@ __host__ __device__ inline int64_t lds_level_bytes(int nx, int ny, int lds_cells
     int lx = nx, ly = ny;
     const int L = num_levels(ny);
     for (int l = 0; l < L; ++l) {
+        if (lx * ly <= lds_cells) return b + wave_top_bytes<T>(lx, ly) + wave_region_bytes<T>(lx);
         if (level_in_lds(l, lx * ly, lds_cells, lds_block_cells)) b += level_bytes<T>(lx, ly);
         lx >>= 1; ly >>= 1;
     }
@@ -279,7 +327,8 @@ __device__ inline void bind_history(Solve<T>& S, uint8_t* base) {
 // arrays in the workgroup's LDS (`lds`): they are rebuilt every iteration,
 // so nothing there has to survive a launch.  Every level keeps its region
 // in the workspace too (S.hg views that of level lb).  lds_cells >= 2, so
-// the coarsest level (2 x 1) is always in LDS and S.lds_from < S.L.
+// the coarsest level (2 x 1) is always in LDS and S.lds_from < S.L; the
+// levels after S.lds_from are places of the wave region and are not bound.
 template <typename T>
 __device__ inline void bind_solve(Solve<T>& S, uint8_t* base, int nx, int ny, uint8_t* lds, int lds_cells,
                                   int lds_block_cells) {
@@ -300,12 +349,17 @@ __device__ inline void bind_solve(Solve<T>& S, uint8_t* base, int nx, int ny, ui
     S.lb = S.L;
     S.lc = 0;
     S.hand = 0;
-    auto bind_level = [](Level<T>& v, T* a, int lx, int ly) {
+    S.wave = nullptr;
+    auto bind_level = [](Level<T>& v, T* a, int lx, int ly, bool with_r = true) {
         const int m = lx * ly;
         v.nx = lx; v.ny = ly;
-        v.x = a; v.b = a + m; v.r = a + 2 * m; v.te = a + 3 * m; v.tn = a + 4 * m; v.acc = a + 5 * m;
-        v.mx = a + 6 * m; v.my = a + 7 * m; v.dx = a + 8 * m; v.dy = a + 9 * m;
-        v.dl = a + 10 * m; v.dr = a + 10 * m + ly; v.mr = a + 10 * m + 2 * ly; v.ml = a + 10 * m + 3 * ly;
+        v.x = a; v.b = a + m;
+        T* f = a + (with_r ? 3 : 2) * m;
+        v.r = with_r ? a + 2 * m : nullptr;
+        v.te = f; v.tn = f + m; v.acc = f + 2 * m; v.mx = f + 3 * m; v.my = f + 4 * m; v.dx = f + 5 * m;
+        v.dy = f + 6 * m;
+        f += 7 * m;
+        v.dl = f; v.dr = f + ly; v.mr = f + 2 * ly; v.ml = f + 3 * ly;
     };
     for (int l = 0; l < S.L; ++l) {
         const bool in_lds = level_in_lds(l, lx * ly, lds_cells, lds_block_cells);
@@ -313,7 +367,12 @@ __device__ inline void bind_solve(Solve<T>& S, uint8_t* base, int nx, int ny, ui
             S.lb = l;
             bind_level(S.hg, reinterpret_cast<T*>(q), lx, ly);
         }
-        if (lx * ly <= lds_cells && S.lds_from == S.L) S.lds_from = l;
+        if (lx * ly <= lds_cells) {
+            S.lds_from = l;
+            bind_level(S.lv[l], reinterpret_cast<T*>(ql), lx, ly, false);
+            S.wave = reinterpret_cast<T*>(ql + wave_top_bytes<T>(lx, ly));
+            break;
+        }
         bind_level(S.lv[l], reinterpret_cast<T*>(in_lds ? ql : q), lx, ly);
         if (in_lds) ql += level_bytes<T>(lx, ly);
         q += level_bytes<T>(lx, ly);
@@ -985,9 +1044,8 @@ __device__ void coarsen_cluster(Solve<T>& S) {
     }
 }
 
-// Levels `from` .. L-1, run by the leader alone: its workgroup forms the
-// levels whose finer neighbour is in global memory or in the workgroup's
-// part of LDS, wavefront 0 the rest (LDS levels, from LDS levels).
+// Levels `from` .. lds_from, by the leader's workgroup alone; wavefront 0's
+// cycle forms the coarser ones itself.
 template <typename T, bool kTransport>
 __device__ void coarsen_leader(Solve<T>& S, int from) {
     const int lw = S.lds_from, lb = S.lb;
@@ -997,21 +1055,14 @@ __device__ void coarsen_leader(Solve<T>& S, int from) {
         else coarsen_level<T, kTransport, BlockTeam, 3, 3>(S.lv[l - 1], S.lv[l]);
         __syncthreads();
     }
-    if (threadIdx.x < kWave) {
-        for (int l = (from > lw + 1 ? from : lw + 1); l < S.L; ++l) {
-            coarsen_level<T, kTransport, WaveTeam, 3, 3>(S.lv[l - 1], S.lv[l]);
-            WaveTeam::sync();
-        }
-    }
-    __syncthreads();
 }
 
 template <typename T, bool kTransport>
 __device__ void handoff_in(Solve<T>& S);
 
-// Every level, complete on return (the adjoint's transposed solves reuse
-// the coefficients over several cycles; a level handed from the cluster to
-// the leader's LDS is copied there first).
+// Every level down to lds_from, complete on return (the adjoint's transposed
+// solves reuse the coefficients over several cycles; a level handed from the
+// cluster to the leader's LDS is copied there first).
 template <typename T, bool kTransport>
 __device__ void coarsen(Solve<T>& S) {
     coarsen_cluster<T, kTransport>(S);
@@ -1509,8 +1560,7 @@ __device__ __attribute__((noinline)) void line_sweep_m(Level<T>& v0, int col) {
 // line in one wavefront; y-lines of 64 to 256 rows take four, so that a
 // wavefront holds two or more neighbouring columns and each of its loads
 // touches half as many (or fewer) cache lines as with one column of strided
-// rows.  The wavefront-team levels (at most 512 cells) have lines of at most
-// 32 cells: two rows per lane.
+// rows.
 // x-lines of 512 and 1024 cells on the cluster levels (one wavefront per
 // line, MS = 8 or 16 rows per lane).  line_sweep_m gathers a lane's MS
 // consecutive cells, so each of its load instructions touches 32 cache lines
@@ -1665,9 +1715,7 @@ __device__ void line_sweep(Level<T>& v, int col) {
             return;
         }
     }
-    if constexpr (std::is_same<Team, WaveTeam>::value) {
-        line_sweep_m<T, kXLine, kTrans, 2, Team, AS>(v, col);
-    } else if constexpr (kXLine) {
+    if constexpr (kXLine) {
         // rows of 64 and 128 cells: 16 or 32 lanes per line, so that a
         // wavefront solves two or four lines at once with fewer reduction
         // steps (128x64 group 188 -> 179 ms, 64x32 86 -> 80 ms)
@@ -1684,9 +1732,7 @@ __device__ void line_sweep(Level<T>& v, int col) {
 
 // One zebra sweep in one direction: x-lines (even rows, then odd rows) or
 // y-lines (even columns, then odd columns; a one-row level has only its
-// x-line).  The transport V-cycle pre-smooths with x-lines; it post-smooths
-// with y-lines on the coarse (LDS) levels, so every cycle relaxes along
-// both directions.
+// x-line).
 template <typename T, bool kTrans = false, class Team = BlockTeam, int AS = 0>
 __device__ void line_smooth(Level<T>& v, bool ylines) {
     if (ylines && v.ny > 1) {
@@ -1697,6 +1743,8 @@ __device__ void line_smooth(Level<T>& v, bool ylines) {
         line_sweep<T, true, kTrans, Team, AS>(v, 1);
     }
 }
+
+#include "henry_wave.hpp"
 
 // ------------------------------------------------------------------ V-cycles
 // Downward leg on level l (address space AS; level l+1 in ASN): smooth,
@@ -1714,19 +1762,18 @@ __device__ void vdown(Solve<T>& S, int l) {
 }
 
 // Upward leg on level l: prolongation from level l+1, smooth.  The
-// transport post-smoothing takes y-lines on the levels wavefront 0 runs and
-// x-lines on the larger ones: in global memory a y-line sweep costs about
-// three x-line sweeps (the rows of a column are a cache line apart), and
-// the outer iteration counts stay the same (1.69 per step on 256x128/800
-// either way); the cycle still relaxes along y on every level of 512 cells
-// or fewer.
+// transport post-smoothing takes x-lines here and y-lines on the levels of
+// 512 cells or fewer (henry_wave.hpp): in global memory a y-line sweep costs
+// about three x-line sweeps (the rows of a column are a cache line apart),
+// and the outer iteration counts stay the same (1.69 per step on 256x128/800
+// either way).
 template <typename T, bool kTransport, bool kTrans, class Team, int AS, int ASN>
 __device__ void vup(Solve<T>& S, int l) {
     Level<T>& v = S.lv[l];
     const Level<T>& c = (S.hand && l + 1 == S.lc) ? S.hg : S.lv[l + 1];
     prolong_add<T, Team, ASN, AS, !kTransport>(c, v);
     Team::sync();
-    if constexpr (kTransport) line_smooth<T, kTrans, Team, AS>(v, std::is_same<Team, WaveTeam>::value);
+    if constexpr (kTransport) line_smooth<T, kTrans, Team, AS>(v, false);
     else rbgs<T, Team, AS>(v, 2);
 }
 
@@ -1763,34 +1810,16 @@ __device__ void handoff_out(Solve<T>& S) {
     for (int i = threadIdx.x; i < n; i += blockDim.x) G.x[i] = D.x[i];
 }
 
-// The coarsest level of every hierarchy has one row (ny = 1, nx = 2): the
-// system is a single x-line, solved exactly.
-template <typename T, bool kTransport, bool kTrans, class Team, int AS>
-__device__ void vcoarsest(Solve<T>& S) {
-    if constexpr (kTransport) line_sweep<T, true, kTrans, Team, AS>(S.lv[S.L - 1], 0);
-    else {
-        const LV<T, AS> v(S.lv[S.L - 1]);
-        // pressure coarsest (2 x 1 cells): direct solve of the 2 x 2 system
-        if (Team::rank() == 0) {
-            const Stencil<T> s0 = pstencil(v, NbS(0, 0, 2, 1)), s1 = pstencil(v, NbS(1, 0, 2, 1));
-            const T det = s0.d * s1.d - s0.e * s1.w;
-            v.x[0] = (v.b[0] * s1.d + s0.e * v.b[1]) / det;
-            v.x[1] = (s0.d * v.b[1] + s1.w * v.b[0]) / det;
-        }
-        Team::sync();
-    }
-}
-
 // One V-cycle.  The cluster levels (0 .. lc-1) are run by the whole
 // cluster; the leader alone runs the rest: its workgroup the levels in
-// global memory, and from the first level in LDS (S.lds_from; the coarsest
-// level always is) down to the coarsest and back, its wavefront 0 alone
-// while the other wavefronts wait at one barrier.  With coarse_coeffs the
-// leader first forms the coefficients of levels lc+1 .. L-1 (the cluster
-// formed levels 1 .. lc before the cycle).
+// global memory or in its part of LDS, and from the first level of at most
+// lds_cells cells (S.lds_from; the coarsest level always is) down to the
+// coarsest and back, its wavefront 0 alone while the other wavefronts wait at
+// one barrier.  With coarse_coeffs the leader first forms the coefficients of
+// levels lc+1 .. lds_from (the cluster formed levels 1 .. lc before the
+// cycle).
 template <typename T, bool kTransport, bool kTrans = false>
 __device__ void vcycle(Solve<T>& S, PhaseClock* pc = nullptr, bool coarse_coeffs = false) {
-    const int L = S.L;
     const int lw = S.lds_from;
     const int lc = S.lc;
     const int t0 = kTransport ? 16 : 8;
@@ -1812,11 +1841,7 @@ __device__ void vcycle(Solve<T>& S, PhaseClock* pc = nullptr, bool coarse_coeffs
             else vdown<T, kTransport, kTrans, BlockTeam, 3, 3>(S, l);
             if (pc) pc->tick(t0 + (l == 0 ? 1 : 2));
         }
-        if (threadIdx.x < kWave) {
-            for (int l = lw; l < L - 1; ++l) vdown<T, kTransport, kTrans, WaveTeam, 3, 3>(S, l);
-            vcoarsest<T, kTransport, kTrans, WaveTeam, 3>(S);
-            for (int l = L - 2; l >= lw; --l) vup<T, kTransport, kTrans, WaveTeam, 3, 3>(S, l);
-        }
+        if (threadIdx.x < kWave) wave_cycle<T, kTransport, kTrans>(S.lv[lw], S.wave);
         __syncthreads();
         if (pc) pc->tick(t0 + 3);
         for (int l = lw - 1; l >= lc; --l) {

@@ -1133,24 +1133,30 @@ int mlmc_level_estimate(henry_ctx* ctx, int32_t L, const henry_grid_t* fine, con
     }
     DeviceGuard dg(ctx->device);
     hipStream_t s0 = reinterpret_cast<hipStream_t>(stream);
-    henry::LevelPtrs lp{};
+    henry::FieldLevels f{};
+    f.nlev = L + 1;
+    f.qstats = qstats;
+    f.var_est = var_est;
+    int blocks = 0;
     for (int l = 0; l <= L; ++l) {
-        const int nx = fine[l].nx, ny = fine[l].ny;
-        const double* cc = l > 0 ? c_coarse[l] : nullptr;
-        const double* qc = l > 0 ? q_coarse[l] : nullptr;
-        const int cells = nx * ny;
-        const int blocks = (cells * 64 + 255) / 256;
-        hipLaunchKernelGGL(henry::mlmc_field_stats_kernel, dim3(blocks), dim3(256), 0, s0, c_fine[l], cc, m[l], nx,
-                           ny, mean_Y[l], var_Y[l]);
-        hipLaunchKernelGGL(henry::mlmc_qoi_stats_kernel, dim3(1), dim3(64), 0, s0, q_fine[l], qc, m[l],
-                           qstats + 2 * l);
-        lp.mean[l] = mean_Y[l];
-        lp.var[l] = var_Y[l];
-        lp.m[l] = m[l];
-        lp.nx[l] = nx;
+        const int cells = fine[l].nx * fine[l].ny;
+        f.cf[l] = c_fine[l];
+        f.cc[l] = l > 0 ? c_coarse[l] : nullptr;
+        f.qf[l] = q_fine[l];
+        f.qc[l] = l > 0 ? q_coarse[l] : nullptr;
+        f.mean[l] = mean_Y[l];
+        f.var[l] = var_Y[l];
+        f.m[l] = m[l];
+        f.nx[l] = fine[l].nx;
+        f.per_cell[l] = henry::field_threads_per_cell(m[l], cells);
+        f.first[l] = blocks;
+        const int tile = henry::kFieldThreads / f.per_cell[l];
+        blocks += (cells + tile - 1) / tile;
     }
-    hipLaunchKernelGGL(henry::mlmc_combine_kernel, dim3(1), dim3(1024), 0, s0, lp, L, fine[L].nx, fine[L].ny,
-                       qstats, Ec_finest, var_est);
+    f.first[L + 1] = blocks;
+    hipLaunchKernelGGL(henry::mlmc_level_stats_kernel, dim3(blocks + f.nlev), dim3(henry::kFieldThreads), 0, s0, f);
+    hipLaunchKernelGGL(henry::mlmc_combine_kernel, dim3((fine[L].nx * fine[L].ny + 255) / 256), dim3(256), 0, s0, f,
+                       Ec_finest);
     if (hipGetLastError() != hipSuccess) return HENRY_EHIP;
     return HENRY_OK;
 }
@@ -1218,8 +1224,17 @@ int henry_sample_stats(henry_ctx* ctx, int32_t nsamples, int32_t nvals, const do
         for (P = 1; P < nsamples;) P <<= 1;
     DeviceGuard dg(ctx->device);
     hipStream_t s0 = reinterpret_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(henry::sample_stats_kernel, dim3(nvals), dim3(256), (size_t)P * sizeof(double), s0, x,
-                       x_sub, nsamples, nvals, P, pr, mean_out, var_out, q_out);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((nvals + 7) / 8 * 8), dim3(henry::kStatThreads), 0, s0, x, x_sub, nsamples, nvals, pr, mean_out,
+                           var_out, q_out);
+    };
+    if (P == 0) launch(henry::sample_moments_kernel);
+    else if (P <= 256) launch(henry::sample_stats_kernel<1>);
+    else if (P == 512) launch(henry::sample_stats_kernel<2>);
+    else if (P == 1024) launch(henry::sample_stats_kernel<4>);
+    else if (P == 2048) launch(henry::sample_stats_kernel<8>);
+    else if (P == 4096) launch(henry::sample_stats_kernel<16>);
+    else launch(henry::sample_stats_kernel<32>);
     if (hipGetLastError() != hipSuccess) return HENRY_EHIP;
     return HENRY_OK;
 }

@@ -441,6 +441,34 @@ __device__ inline T qdiv(T a, T b) {
     else return a / b;
 }
 
+// ------------------------------------------------------------------ vectors and lanes
+template <typename T> using LdsPtr = typename AsPtr<T, 3>::type;
+template <typename T> using Vec2 = T __attribute__((ext_vector_type(2)));
+template <typename T> using Vec4 = T __attribute__((ext_vector_type(4)));
+
+template <typename T>
+__device__ inline Vec2<T> lds_load2(LdsPtr<T> p) { return *(typename AsPtr<Vec2<T>, 3>::type)p; }
+template <typename T>
+__device__ inline void lds_store2(LdsPtr<T> p, T a, T b) {
+    Vec2<T> v = {a, b};
+    *(typename AsPtr<Vec2<T>, 3>::type)p = v;
+}
+
+// Value of the lane kN below (above) within its row of 16 lanes; 0 where
+// the row ends.
+template <int kCtrl>
+__device__ inline float dpp_row(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xf, 0xf, true));
+}
+template <int kCtrl>
+__device__ inline double dpp_row(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+template <int kN, typename T> __device__ inline T lane_below(T v) { return dpp_row<0x110 + kN>(v); }  // row_shr
+template <int kN, typename T> __device__ inline T lane_above(T v) { return dpp_row<0x100 + kN>(v); }  // row_shl
+
 // ------------------------------------------------------------------ teams
 // The threads that run one multigrid operation together: the whole
 // workgroup (levels in global memory), or wavefront 0 alone (the coarse
@@ -1705,6 +1733,168 @@ __device__ __attribute__((noinline)) void line_sweep_x_staged(Level<T>& v0, int 
     ClusterTeam::sync();
 }
 
+// x-lines of 64, 128 and 256 cells: line_sweep_m's solve with four rows per
+// lane, TL = 16, 32 or 64 lanes per line.  With one load per cell and array
+// (12 of them), a wavefront's loads lay 16 bytes apart and each took the
+// texture unit 16 clocks for a quarter of the bytes it moved; that, not the
+// elimination, was the phase.  Here a lane loads its four cells of an array
+// as one vector (the flux into the segment's first cell comes from the lane
+// before), 10 loads instead of 48: an outer iteration of 128x64 (one
+// workgroup) 190 -> 172 us, its level 0 transport legs 22.2 -> 15.7 and 14.9
+// -> 8.8 us.
+//
+// Lane l of a line's rows of 16 holds segment t = (l mod 16) R + l / 16,
+// R = TL / 16: a shift by a multiple of R segments is then a shift within
+// rows of 16 lanes, a DPP operand, and only the log2(R) shortest shifts of
+// the cyclic reduction go through the LDS crossbar.  A reduction step's two
+// reciprocals are one, formed before the shift.
+template <int TL>
+struct LineLanes {
+    static constexpr int R = TL / 16;
+    __device__ static inline int segment(int lane) { return (lane & 15) * R + ((lane >> 4) & (R - 1)); }
+    __device__ static inline int line(int lane) { return (lane >> 4) / R; }
+    __device__ static inline int lane_of(int lane, int t) { return (lane & ~(TL - 1)) | ((t & (R - 1)) << 4) | (t / R); }
+    // value of segment t - kS (below), t + kS (above) of the same line; any
+    // finite value of this wavefront's where there is none
+    template <int kS, typename T>
+    __device__ static inline T below(T v, int lane) {
+        if constexpr (kS % R == 0) return lane_below<kS / R>(v);
+        else { const int t = segment(lane); return __shfl(v, t >= kS ? lane_of(lane, t - kS) : lane, kWave); }
+    }
+    template <int kS, typename T>
+    __device__ static inline T above(T v, int lane) {
+        if constexpr (kS % R == 0) return lane_above<kS / R>(v);
+        else { const int t = segment(lane); return __shfl(v, t + kS < TL ? lane_of(lane, t + kS) : lane, kWave); }
+    }
+};
+
+// One step of the cyclic reduction over a line's segments and those after
+// it (segments without a partner have a zero coupling to it).
+template <int kS, int TL, typename T>
+__device__ inline void line_pcr(T& A, T& B, T& C, T& D, int lane) {
+    if constexpr (kS < TL) {
+        using LL = LineLanes<TL>;
+        T k1, k2;
+        if constexpr (sizeof(T) == 4) {
+            const T rB = __builtin_amdgcn_rcpf(B);
+            k1 = A * LL::template below<kS>(rB, lane);
+            k2 = C * LL::template above<kS>(rB, lane);
+        } else {
+            const int t = LL::segment(lane);
+            const T Bl = LL::template below<kS>(B, lane), Br = LL::template above<kS>(B, lane);
+            k1 = t >= kS ? A / Bl : (T)0;
+            k2 = t + kS < TL ? C / Br : (T)0;
+        }
+        const T Al = LL::template below<kS>(A, lane), Cl = LL::template below<kS>(C, lane),
+                Dl = LL::template below<kS>(D, lane);
+        const T Ar = LL::template above<kS>(A, lane), Cr = LL::template above<kS>(C, lane),
+                Dr = LL::template above<kS>(D, lane);
+        T nB = B, nD = D;
+        nB -= Cl * k1;
+        nD -= Dl * k1;
+        nB -= Ar * k2;
+        nD -= Dr * k2;
+        A = -Al * k1;
+        C = -Cr * k2;
+        B = nB;
+        D = nD;
+        line_pcr<2 * kS, TL>(A, B, C, D, lane);
+    }
+}
+
+template <typename T, bool kTrans, int TL, class Team, int AS>
+__device__ __attribute__((noinline)) void line_sweep_x(Level<T>& v0, int col) {
+    using LL = LineLanes<TL>;
+    using V4 = Vec4<T>;
+    constexpr int MS = 4, nx = MS * TL;
+    const LV<T, AS> v(v0);
+    const int ny = v.ny;
+    const int nlines = (ny - col + 1) >> 1;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int t = LL::segment(lane);
+    const bool first = t == 0, last = t == TL - 1;
+    const int need = nlines * TL;
+    auto load4 = [](typename LV<T, AS>::P p) { return *(typename AsPtr<V4, AS>::type)p; };
+    for (int base = 0; base < need; base += Team::size()) {
+        const int li = (base + Team::rank() - lane) / TL + LL::line(lane);
+        const bool active = li < nlines;
+        const int j = col + 2 * (active ? li : 0);
+        const bool hs = j > 0, hn = j + 1 < ny;
+        const int k0 = j * nx + MS * t, ks = hs ? k0 - nx : k0, kn = hn ? k0 + nx : k0;
+        const V4 acc = load4(v.acc + k0), mE = load4(v.mx + k0), dE = load4(v.dx + k0), mN = load4(v.my + k0),
+                 dN = load4(v.dy + k0), mS = load4(v.my + ks), dS = load4(v.dy + ks), bq = load4(v.b + k0),
+                 xS = load4(v.x + ks), xN = load4(v.x + kn);
+        const T bE = pos(-v.mr[j]) + v.dr[j], bW = v.dl[j] + v.ml[j];
+        const T mW0 = LL::template below<1>((T)mE[3], lane), dW0 = LL::template below<1>((T)dE[3], lane);
+        T cp[MS], y[MS], u[MS];
+        T wlast = (T)0;
+        T ar = (T)0, br = (T)1, cr = (T)0, dr = (T)0;
+#pragma unroll
+        for (int q = 0; q < MS; ++q) {
+            const bool he = q < MS - 1 || !last, hw = q > 0 || !first;
+            const T mW = q == 0 ? mW0 : mE[q > 0 ? q - 1 : 0], dW = q == 0 ? dW0 : dE[q > 0 ? q - 1 : 0];
+            // cstencil's / cstencil_t's couplings and diagonal
+            const T ce = pos(-mE[q]) + dE[q], cw = pos(mW) + dW, cn = pos(-mN[q]) + dN[q], cs = pos(mS[q]) + dS[q];
+            T d = acc[q];
+            d += he ? ce : bE;
+            d += hw ? cw : bW;
+            d += hn ? cn : (T)0;
+            d += hs ? cs : (T)0;
+            const T e = he ? (kTrans ? pos(mE[q]) + dE[q] : ce) : (T)0, w = hw ? (kTrans ? pos(-mW) + dW : cw) : (T)0,
+                    n = hn ? (kTrans ? pos(mN[q]) + dN[q] : cn) : (T)0,
+                    s = hs ? (kTrans ? pos(-mS[q]) + dS[q] : cs) : (T)0;
+            T rhs = bq[q];
+            rhs += s * xS[q];
+            rhs += n * xN[q];
+            const T a = -w, c = -e;
+            if (q < MS - 1) {
+                const T den = (q > 0) ? d - a * cp[q > 0 ? q - 1 : 0] : d;
+                const T inv = qdiv((T)1, den);
+                const T yprev = (q > 0) ? y[q > 0 ? q - 1 : 0] : (T)0;
+                const T uprev = (q > 0) ? u[q > 0 ? q - 1 : 0] : (T)0;
+                cp[q] = c * inv;
+                y[q] = (rhs - a * yprev) * inv;
+                u[q] = ((q == 0 ? -a : (T)0) - a * uprev) * inv;
+                if (q == MS - 2) wlast = (-c - a * (T)0) * inv;
+            } else {
+                ar = a; br = d; cr = c; dr = rhs;
+            }
+        }
+        // back substitution of the interior rows (coupling to iota_t: the
+        // running product wrun, w[q] = 0 - cp[q] w[q + 1])
+        T wrun = wlast;
+#pragma unroll
+        for (int q = MS - 3; q >= 0; --q) {
+            y[q] -= cp[q] * y[q + 1];
+            u[q] -= cp[q] * u[q + 1];
+            wrun = (T)0 - cp[q] * wrun;
+        }
+        // interface equation of the segment's last row (the last segment's
+        // coupling to a next one, cr, is zero)
+        const T yN = LL::template above<1>(y[0], lane), uN = LL::template above<1>(u[0], lane),
+                wN = LL::template above<1>(wrun, lane);
+        T A = ar * u[MS - 2];
+        T B = br + ar * wlast + cr * uN;
+        T C = cr * wN;
+        T D = dr - ar * y[MS - 2] - cr * yN;
+        line_pcr<1, TL>(A, B, C, D, lane);
+        const T iota = qdiv(D, B);
+        const T left = LL::template below<1>(iota, lane);  // the first segment's coupling to it, u, is zero
+        if (active) {
+            V4 x;
+            x[MS - 1] = iota;
+            T wq = wlast;
+#pragma unroll
+            for (int q = MS - 2; q >= 0; --q) {
+                if (q < MS - 2) wq = (T)0 - cp[q] * wq;
+                x[q] = y[q] + u[q] * left + wq * iota;
+            }
+            *(typename AsPtr<V4, AS>::type)(v.x + k0) = x;
+        }
+    }
+    Team::sync();
+}
+
 template <typename T, bool kXLine, bool kTrans = false, class Team = BlockTeam, int AS = 0>
 __device__ void line_sweep(Level<T>& v, int col) {
     const int len = kXLine ? v.nx : v.ny;  // 2 .. 1024, a power of two
@@ -1716,11 +1906,10 @@ __device__ void line_sweep(Level<T>& v, int col) {
         }
     }
     if constexpr (kXLine) {
-        // rows of 64 and 128 cells: 16 or 32 lanes per line, so that a
-        // wavefront solves two or four lines at once with fewer reduction
-        // steps (128x64 group 188 -> 179 ms, 64x32 86 -> 80 ms)
         if (len < 64) line_sweep_m<T, kXLine, kTrans, 2, Team, AS>(v, col);
-        else if (len <= 256) line_sweep_m<T, kXLine, kTrans, 4, Team, AS>(v, col);
+        else if (len == 64) line_sweep_x<T, kTrans, 16, Team, AS>(v, col);
+        else if (len == 128) line_sweep_x<T, kTrans, 32, Team, AS>(v, col);
+        else if (len == 256) line_sweep_x<T, kTrans, 64, Team, AS>(v, col);
         else if (len == 512) line_sweep_m<T, kXLine, kTrans, 8, Team, AS>(v, col);
         else line_sweep_m<T, kXLine, kTrans, 16, Team, AS>(v, col);
     } else {

@@ -23,33 +23,6 @@
 //   16x8 and below   pressure 10.5 -> 3.0 us, transport 14.7 -> 4.2 us
 #pragma once
 
-template <typename T> using LdsPtr = typename AsPtr<T, 3>::type;
-template <typename T> using Vec2 = T __attribute__((ext_vector_type(2)));
-template <typename T> using Vec4 = T __attribute__((ext_vector_type(4)));
-
-template <typename T>
-__device__ inline Vec2<T> lds_load2(LdsPtr<T> p) { return *(typename AsPtr<Vec2<T>, 3>::type)p; }
-template <typename T>
-__device__ inline void lds_store2(LdsPtr<T> p, T a, T b) {
-    Vec2<T> v = {a, b};
-    *(typename AsPtr<Vec2<T>, 3>::type)p = v;
-}
-
-// Value of the lane kN below (above) within its row of 16 lanes; 0 where
-// the row ends.
-template <int kCtrl>
-__device__ inline float dpp_row(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xf, 0xf, true));
-}
-template <int kCtrl>
-__device__ inline double dpp_row(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-template <int kN, typename T> __device__ inline T lane_below(T v) { return dpp_row<0x110 + kN>(v); }  // row_shr
-template <int kN, typename T> __device__ inline T lane_above(T v) { return dpp_row<0x100 + kN>(v); }  // row_shl
-
 __device__ inline int wave_lane() { return (int)threadIdx.x & (kWave - 1); }
 
 template <typename T, int kElems>

@@ -164,13 +164,13 @@ __host__ __device__ inline int64_t level_bytes(int nx, int ny) {
 // then the older states c2, p2 (u^{n-2}), c3, p3 (u^{n-3}) and c4, p4
 // (u^{n-4}) of the extrapolated initial guess (their roles rotate: bind_history), then kScratch doubles of
 // scratch: [0] recharge, [1] status, [2] outer iterations, [3] converged states in a row, [4] the history's
-// rotation at the end of a launch, [8..31] phase timers of builds with
-// HENRY_PHASE_TIMERS, [32..63] the state of a cluster of workgroups sharing the solve (the members'
+// rotation at the end of a launch, [6] the arrivals and failures of a cluster on one XCD, [8..31]
+// phase timers of builds with HENRY_PHASE_TIMERS, [32..63] the state of a cluster of workgroups sharing the solve (the members'
 // 32-bit arrival counts in [32..35], the error flag in [36], barriers passed [37], the members' XCD
 // ids [40..47], their partial residual norms [48..63]).
 enum : int { kP, kC, kCn, kPhi, kK, kPp, kTx, kTy, kWx, kWy, kIsc, kC2, kP2, kC3, kP3, kC4, kP4, kF64Arrays };
 constexpr int kScratch = 64;
-constexpr int kClusterFlags = 32, kClusterErr = 36, kClusterGen = 37, kClusterXcc = 40, kClusterSlots = 48;
+constexpr int kClusterHere = 6, kClusterFlags = 32, kClusterErr = 36, kClusterGen = 37, kClusterXcc = 40, kClusterSlots = 48;
 constexpr int kMaxCluster = 8;
 // the barrier polls the K arrival counts and the error flag in one load:
 // the flag sits past the last count, within one wavefront's lanes
@@ -504,22 +504,25 @@ struct WaveTeam {
 // are dealt to the eight XCDs round robin (block b on XCD b mod 8), so the
 // members of cluster c on XCD x are K consecutive blocks of that XCD's
 // sequence.  Each launch checks the placement (hardware XCC id, exchanged
-// under an agent-scope barrier); the clusters whose members share one XCD,
-// and so one L2, synchronise by waiting for their own stores, a relaxed
-// store of the member's arrival count and an acquire poll of all members'
-// counts in one load (L1 invalidated); any other cluster uses the
-// agent-scope release (L2 write-back) instead.  Blocks of one XCD are
-// dispatched in order, so the lowest cluster not yet complete always gets
-// its members.  Every wait is bounded (Launch::cluster_wait, 10 s by
-// default): past it a member raises the cluster's error flag, every later
-// barrier of the cluster returns at once, and the solve reports
-// HENRY_STATUS_SYNC.
+// under an agent-scope barrier).  Clusters whose members share one XCD, and
+// so one L2, synchronise through an atomic counter in that L2: each member's
+// arrival is one atomic that returns the count, so the last to arrive does
+// not poll, and the others poll with atomics too (the texture cache does not
+// hold them); then the L1 is invalidated.  Any other cluster uses
+// agent-scope stores and loads of the members' counts, with a release (L2
+// write-back) before.  Blocks of one XCD are dispatched in order, so the
+// lowest cluster not yet complete always gets its members.  Every wait is
+// bounded (Launch::cluster_wait, 10 s by default): past it a member raises
+// the cluster's error flag, every later barrier of the cluster returns at
+// once, and the solve reports HENRY_STATUS_SYNC.
 struct ClusterState {
     int K, member, base, size;
     unsigned* flags; // [K] barriers each member has arrived at
     unsigned* err;   // sticky error flag
+    unsigned long long* here;  // members on one XCD: arrivals of this launch, failures from bit 56 on
     double* slots;   // [2K] partial norms
     unsigned gen;    // barriers passed
+    unsigned long long gen_here;  // of them through `here`, this launch
     int local;       // all members on one XCD
     int failed;
     uint64_t wait;   // bound of one wait (wall-clock ticks)
@@ -530,38 +533,86 @@ __shared__ ClusterState g_cl;
 
 __device__ inline int xcc_id() { return __builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)); }
 
+// Adds v to a cluster's counter in the L2 of the calling XCD and returns the
+// value before.  Written out, with its wait, because the atomic must be
+// performed in that L2 (no sc1: device scope would send it past it, to the
+// point where the XCDs meet) and by the one lane that calls it (the
+// compiler would add a scan over the lanes).
+__device__ inline unsigned long long l2_fetch_add(unsigned long long* p, unsigned long long v) {
+    unsigned long long old;
+    asm volatile("global_atomic_add_x2 %0, %1, %2, off sc0\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(old)
+                 : "v"(p), "v"(v)
+                 : "memory");
+    return old;
+}
+
+constexpr int kFailBit = 56;
+
+// The bound of a wait: the wall clock is first read after a poll that found
+// the members missing (reading it before would delay every barrier by its
+// latency), then every 8 polls.
+struct WaitClock {
+    uint64_t t0;
+    unsigned polls = 0;
+    __device__ inline bool expired(uint64_t wait) {
+        if ((polls++ & 7u) != 0u) return false;
+        const uint64_t t = wall_clock64();
+        if (polls == 1u) t0 = t;
+        return t - t0 > wait;
+    }
+};
+
 // Every workgroup of a cluster waits until all K members have arrived; all
 // memory operations before the call are visible to every member after it.
-// Wavefront 0 publishes the member's arrival count and polls the K counts
-// and the cluster's error flag with one load per lane (lane k < K: member
-// k's count; the lane at the error flag's offset: the flag), relaxed, so
-// that one poll is one L2 round trip; one acquire fence after the counts
-// are all there makes the members' stores visible.  The wall clock is read
-// every 16 polls only.
+// On one XCD lane 0 of wavefront 0 arrives and polls (256x128 at K = 8, 24
+// barriers an iteration: 215 -> 208 us).  Elsewhere wavefront 0 publishes the
+// member's arrival count and polls the K counts and the cluster's error flag
+// with one load per lane (lane k < K: member k's count; the lane at the error
+// flag's offset: the flag), so that one poll is one round trip.  One acquire
+// fence after the members are all there makes their stores visible.
 __device__ inline void cluster_barrier() {
     __builtin_amdgcn_s_waitcnt(0);  // this thread's stores have reached L2
     __syncthreads();
     if (threadIdx.x < kWave) {
         const int lane = (int)threadIdx.x;
         const unsigned gen = g_cl.gen + 1u;
-        if (!g_cl.failed) {
+        bool failed = false;
+        if (g_cl.local && !g_cl.failed) {
             if (lane == 0) {
-                if (g_cl.local) __hip_atomic_store(g_cl.flags + g_cl.member, gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                else __hip_atomic_store(g_cl.flags + g_cl.member, gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                unsigned long long* here = g_cl.here;
+                const unsigned long long all = (g_cl.gen_here + 1ull) * (unsigned)g_cl.K;
+                unsigned long long v = l2_fetch_add(here, 1ull) + 1ull;
+                WaitClock clk;
+                while (v < all || (v >> kFailBit) != 0ull) {
+                    if ((v >> kFailBit) != 0ull || clk.expired(g_cl.wait)) {
+                        failed = true;
+                        break;
+                    }
+                    v = l2_fetch_add(here, 0ull);
+                }
+                if (failed) {
+                    l2_fetch_add(here, 1ull << kFailBit);
+                    __hip_atomic_store(g_cl.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    g_cl.failed = 1;
+                }
+                g_cl.gen_here += 1ull;
             }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        } else if (!g_cl.failed) {
+            if (lane == 0) __hip_atomic_store(g_cl.flags + g_cl.member, gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             const int eoff = (int)(g_cl.err - g_cl.flags);  // the error flag's offset (>= K)
             const bool is_err = lane == eoff;
             const unsigned* f = g_cl.flags + (lane < g_cl.K || is_err ? lane : 0);
-            const uint64_t t0 = wall_clock64();
-            bool failed = false;
-            for (unsigned polls = 1;; ++polls) {
+            WaitClock clk;
+            for (;;) {
                 const unsigned v = __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (__any(is_err && v != 0u)) {
                     failed = true;
                     break;
                 }
                 if (__all(is_err || (int)(v - gen) >= 0)) break;
-                if ((polls & 15u) == 0u && wall_clock64() - t0 > g_cl.wait) {
+                if (clk.expired(g_cl.wait)) {
                     failed = true;
                     break;
                 }
@@ -598,8 +649,8 @@ __device__ inline void cluster_stage(uint8_t* lds, int lds_bytes, int64_t per_wa
 __device__ inline void cluster_init_single() {
     if (threadIdx.x == 0) {
         g_cl.K = 1; g_cl.member = 0; g_cl.base = 0; g_cl.size = (int)blockDim.x;
-        g_cl.flags = nullptr; g_cl.err = nullptr; g_cl.slots = nullptr;
-        g_cl.gen = 0u; g_cl.local = 1; g_cl.failed = 0; g_cl.wait = 0;
+        g_cl.flags = nullptr; g_cl.err = nullptr; g_cl.here = nullptr; g_cl.slots = nullptr;
+        g_cl.gen = 0u; g_cl.gen_here = 0ull; g_cl.local = 1; g_cl.failed = 0; g_cl.wait = 0;
         g_cl.stage = nullptr; g_cl.stage_waves = 0;  // no line staging unless cluster_stage says so
     }
     __syncthreads();
@@ -615,6 +666,9 @@ __device__ inline void cluster_init(int K, int member, double* sp, uint64_t wait
         g_cl.err = reinterpret_cast<unsigned*>(sp + kClusterErr);
         g_cl.slots = sp + kClusterSlots;
         g_cl.gen = (unsigned)sp[kClusterGen];
+        g_cl.gen_here = 0ull;
+        g_cl.here = reinterpret_cast<unsigned long long*>(sp + kClusterHere);
+        if (member == 0) *g_cl.here = 0ull;  // in the L2 of a cluster on one XCD before any member passes the next barrier
         g_cl.local = 0;  // the placement check itself uses the agent-scope protocol
         g_cl.failed = 0;
         g_cl.stage = nullptr; g_cl.stage_waves = 0;  // no line staging unless cluster_stage says so

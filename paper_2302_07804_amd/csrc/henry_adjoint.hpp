@@ -344,9 +344,9 @@ template <typename T>
 __device__ int adjoint_step(const Phys& ph, Solve<T>& S, Adj& A, double* red, int max_it, double tol,
                             double& iters) {
     double np, nc;
-    residual_pass(ph, S, 0, red, np, nc);
+    residual_pass(S, 0, red, np, nc);
     coarsen_pressure(S);
-    residual_pass(ph, S, 1, red, np, nc);
+    residual_pass(S, 1, red, np, nc);
     coarsen_transport(S);
     // scaled norm of the rhs
     // (and the inverse block diagonals of this step for the norms)
@@ -467,6 +467,7 @@ __global__ void __launch_bounds__(512) henry_adjoint_kernel(Launch lp, AdjLaunch
         set_cluster_levels(S, lp.cluster);
         S.nsteps = d.nsteps;
         S.tau = ph.T / d.nsteps;
+        S.ph = ph;
         S.q = S.scratch[0];
         bind_adj(A, lp.ws + d.adj_off, d.nx * d.ny, d.nsteps, al.ckpt);
     }

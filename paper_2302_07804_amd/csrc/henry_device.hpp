@@ -228,6 +228,7 @@ struct Solve {
     int hist;      // rotation of the state history (see bind_history)
     double h, tau;
     double q;  // recharge (m/s)
+    Phys ph;
     double *p, *c, *cn, *phi, *K, *pp, *tx, *ty, *wx, *wy, *isc, *c2, *p2, *c3, *p3, *c4, *p4, *scratch;
     Level<T> lv[kMaxLevels];
     Level<T> hg;  // the global-memory arrays of level lb
@@ -466,8 +467,69 @@ __device__ inline double dpp_row(double v) {
     const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, 0xf, 0xf, true);
     return __hiloint2double(hi, lo);
 }
+// Value of the lane below / above in the wavefront; `end` where it ends.
+template <int kCtrl>
+__device__ inline double dpp_wave(double v, double end) {
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(end), __double2loint(v), kCtrl, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(end), __double2hiint(v), kCtrl, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ inline double wave_below(double v, double end) { return dpp_wave<0x138>(v, end); }  // wave_shr:1
+__device__ inline double wave_above(double v, double end) { return dpp_wave<0x130>(v, end); }  // wave_shl:1
+
+// Values that every lane of the wavefront holds alike, in scalar registers.
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ inline double uniform(double v) {
+    return __hiloint2double(uniform(__double2hiint(v)), uniform(__double2loint(v)));
+}
+template <typename P>
+__device__ inline P* uniform(P* p) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    return reinterpret_cast<P*>((uint64_t)(uint32_t)uniform((int)(uint32_t)v) |
+                                ((uint64_t)(uint32_t)uniform((int)(v >> 32)) << 32));
+}
+// v of lane t (uniform)
+__device__ inline double lane_value(double v, int t) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), t),
+                            __builtin_amdgcn_readlane(__double2loint(v), t));
+}
+
 template <int kN, typename T> __device__ inline T lane_below(T v) { return dpp_row<0x110 + kN>(v); }  // row_shr
 template <int kN, typename T> __device__ inline T lane_above(T v) { return dpp_row<0x100 + kN>(v); }  // row_shl
+
+// ------------------------------------------------------------------ rounding
+// A product that is rounded before it is added to anything.
+template <typename T>
+__device__ inline T rounded_mul(T a, T b) {
+#pragma clang fp contract(off)
+    const T p = a * b;
+    return p;
+}
+
+// Where a sum of two products could be fused either way, the choice is
+// written out, so that the code that runs a level does not change its
+// rounding.
+__device__ inline float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ inline double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// Bilinear prolongation weights 9/16, 3/16, 3/16, 1/16.
+template <typename T>
+__device__ inline T prolonged(T near, T side, T up, T far) {
+    return fused((T)0.0625, far, fused((T)0.5625, near, rounded_mul((T)0.1875, side + up)));
+}
+
+// Diagonal as the smoother divides by it: its reciprocal for float (qdiv's),
+// itself for double.
+template <typename T>
+__device__ inline T diag_prep(T d) {
+    if constexpr (sizeof(T) == 4) return __builtin_amdgcn_rcpf(d);
+    else return d;
+}
+template <typename T>
+__device__ inline T diag_div(T a, T prep) {
+    if constexpr (sizeof(T) == 4) return rounded_mul(a, prep);  // not fused into what it is added to next
+    else return a / prep;
+}
 
 // ------------------------------------------------------------------ teams
 // The threads that run one multigrid operation together: the whole
@@ -751,47 +813,9 @@ struct NbS {
 // ------------------------------------------------------------------ physics (FP64)
 __device__ inline double rho_of(const Phys& ph, double c) { return ph.rho0 + (ph.rho1 - ph.rho0) * c; }
 
-// Mass and salt flux from cell a to its east neighbour b, per metre of
-// depth: harmonic K and phi on the face (precomputed: tx = K_f/mu,
-// wx = phi_f D), arithmetic rho; donor cell.
+// Mass and salt flux through a face, per metre of depth: harmonic K and phi
+// on the face (precomputed: K_f / mu, phi_f D), arithmetic rho; donor cell.
 struct FaceFlux { double M, F, lam, dif; };
-
-// Interior face a|b (b east or north of a); on a north face Darcy's law
-// with gravity (0,-g) adds rho_f g h to the pressure difference.
-template <bool kNorth>
-__device__ inline FaceFlux flux_face(const Phys& ph, double h, double pa, double pb, double ca, double cb, double kf,
-                                     double wf) {
-    FaceFlux f;
-    const double rf = 0.5 * (rho_of(ph, ca) + rho_of(ph, cb));
-    f.lam = rf * kf;
-    f.dif = rf * wf;
-    f.M = kNorth ? -f.lam * ((pb - pa) + rf * ph.g * h) : -f.lam * (pb - pa);
-    f.F = f.M * (f.M >= 0.0 ? ca : cb) - f.dif * (cb - ca);
-    return f;
-}
-
-// Seawater face at x = 2 (half-cell distance): p_B = -rho1 g y, c_B = 1;
-// kf = 2 K_P / mu, wf = 2 phi_P D.
-__device__ inline FaceFlux flux_right(const Phys& ph, double y, double pP, double cP, double kf, double wf) {
-    FaceFlux f;
-    const double rB = 0.5 * (rho_of(ph, cP) + ph.rho1);
-    f.lam = rB * kf;
-    f.dif = rB * wf;
-    f.M = -f.lam * (-ph.rho1 * ph.g * y - pP);
-    f.F = f.M * (f.M >= 0.0 ? cP : 1.0) - f.dif * (1.0 - cP);
-    return f;
-}
-
-// Recharge face at x = 0: inflow rho0 q h of fresh water (c_B = 0).
-__device__ inline FaceFlux flux_left(const Phys& ph, double h, double q, double cP, double phiP) {
-    FaceFlux f;
-    const double rB = 0.5 * (rho_of(ph, cP) + ph.rho0);
-    f.lam = 0.0;
-    f.dif = 2.0 * rB * phiP * ph.D;
-    f.M = -ph.rho0 * q * h;
-    f.F = f.dif * cP;
-    return f;
-}
 
 // Wall-clock accumulators of the phases of one step (builds with
 // HENRY_PHASE_TIMERS only; wall_clock64 runs at a constant 100 MHz).
@@ -833,187 +857,257 @@ __device__ inline FacePair face_pair(const Phys& ph, double Ka, double Kb, doubl
 }
 __device__ inline double res_scale(const Phys& ph, double tau, double h, double f) { return tau / (h * h * f * ph.rho0); }
 
-// Operands of one cell's residual, loaded from clamped indices before any
-// arithmetic (no loads under boundary branches).
-struct ResIn {
-    double cP, cnP, phiP, pP, cE, pE, cW, pW, cN, pN;
-    double txP, wxP, txW, wxW, tyP, wyP, sc;
-};
+struct ResNorms { double p, c; };  // scaled max |R^p|, |R^c|
 
-// The residual of one cell from its operands; both the interior and the
-// boundary flux of a face are formed and the applicable one selected.  The
-// south face's flux fs comes in from the cell below (its north face, the same
-// operation on the same operands); the north face's goes out through fn.
-// Writes the level-0 inner arrays of `mode` and returns the scaled |R^p|,
-// |R^c| through mp, mc.
-template <typename T>
-__device__ inline void res_cell(const Phys& ph, Solve<T>& S, int mode, int idx, int j, const Nb& q, const ResIn& a,
-                                const FaceFlux& fs, FaceFlux& fn_out, double& mp, double& mc) {
-    const double h = S.h, h2t = h * h / S.tau;
-    Level<T>& L0 = S.lv[0];
-    const double rP = rho_of(ph, a.cP), rN = rho_of(ph, a.cnP);
-    double Rp = h2t * a.phiP * (rP - rN);
-    double Rc = h2t * a.phiP * (rP * a.cP - rN * a.cnP);
-    // east face: interior, or the seawater boundary
-    const FaceFlux fe = flux_face<false>(ph, h, a.pP, a.pE, a.cP, a.cE, a.txP, a.wxP);
-    const FaceFlux fr = flux_right(ph, -1.0 + (j + 0.5) * h, a.pP, a.cP, a.txP, a.wxP);
-    Rp += q.he ? fe.M : fr.M;
-    Rc += q.he ? fe.F : fr.F;
-    // west face: interior (flux out of the west neighbour), or recharge
-    const FaceFlux fw = flux_face<false>(ph, h, a.pW, a.pP, a.cW, a.cP, a.txW, a.wxW);
-    const FaceFlux fl = flux_left(ph, h, S.q, a.cP, a.phiP);
-    Rp += q.hw ? -fw.M : fl.M;
-    Rc += q.hw ? -fw.F : fl.F;
-    // north face (the top is impermeable)
-    const FaceFlux fn = flux_face<true>(ph, h, a.pP, a.pN, a.cP, a.cN, a.tyP, a.wyP);
-    fn_out = fn;
-    Rp += q.hn ? fn.M : 0.0;
-    Rc += q.hn ? fn.F : 0.0;
-    // south face (the bottom is impermeable)
-    Rp -= q.hs ? fs.M : 0.0;
-    Rc -= q.hs ? fs.F : 0.0;
-    if (mode == 0) {
-        const int ps = pidx(idx - j * S.nx, j, S.nx);  // pressure cycle: colour-split
-        L0.te[ps] = (T)(q.he ? fe.lam : fr.lam);
-        L0.tn[ps] = (T)(q.hn ? fn.lam : 0.0);
-        L0.b[ps] = (T)(-Rp);
-        L0.x[ps] = (T)0;
-        mp = nanmax(mp, fabs(Rp * a.sc));
-    } else if (mode == 2) {
-        S.rout_p[idx] = Rp;
-        S.rout_c[idx] = Rc;
-    } else {
-        mp = nanmax(mp, fabs(Rp * a.sc));
-        L0.mx[idx] = (T)(q.he ? fe.M : 0.0);
-        L0.dx[idx] = (T)(q.he ? fe.dif : 0.0);
-        L0.my[idx] = (T)(q.hn ? fn.M : 0.0);
-        L0.dy[idx] = (T)(q.hn ? fn.dif : 0.0);
-        if (!q.he) { L0.dr[j] = (T)fr.dif; L0.mr[j] = (T)fr.M; }
-        if (!q.hw) { L0.dl[j] = (T)fl.dif; L0.ml[j] = (T)(-fl.M); }
-        L0.acc[idx] = (T)(h2t * a.phiP * rN);
-        L0.b[idx] = (T)(-(Rc - a.cP * Rp));
-        L0.x[idx] = (T)0;
-    }
-    mc = nanmax(mc, fabs(Rc * a.sc));
+// Mass and salt flux of an interior or boundary face: rf the face density,
+// dp the pressure difference (with the gravity term on north faces), ca and
+// cb the upstream candidates of the two directions.
+__device__ inline FaceFlux face_flux(double rf, double dp, double ca, double cb, double kf, double wf) {
+    FaceFlux f;
+    f.lam = rf * kf;
+    f.dif = rf * wf;
+    f.M = rounded_mul(-f.lam, dp);
+    f.F = fused(f.M, f.M >= 0.0 ? ca : cb, -rounded_mul(f.dif, cb - ca));
+    return f;
+}
+// Interior face a|b; on a north face Darcy's law with gravity (0,-g) adds
+// rho_f g h to the pressure difference.
+template <bool kNorth>
+__device__ inline FaceFlux face_flux(const Phys& ph, double h, double ra, double rb, double pa, double pb, double ca,
+                                     double cb, double kf, double wf) {
+    const double rf = 0.5 * (ra + rb);
+    return face_flux(rf, kNorth ? fused(rf * ph.g, h, pb - pa) : pb - pa, ca, cb, kf, wf);
 }
 
-// The rows of one residual pass (see residual_pass).  kFields: the face
-// coefficients and the norm scale formed from K and phi (5 FP64 loads per
-// cell instead of 9, and three FP64 divisions), with the same operations as
-// the fields kernel's stored ones, so both variants give the same bits.
-template <bool kFields, typename T>
-__device__ inline void residual_rows(const Phys& ph, Solve<T>& S, int mode, double& mp, double& mc) {
-    const int nx = S.nx, ny = S.ny;
-    const int bs = ClusterTeam::size(), rk = ClusterTeam::rank();
+// Max of |v| and a maximum so far, on the bit patterns: those of the
+// non-negative doubles are ordered, and a NaN's is above infinity's.
+__device__ inline void abs_max(unsigned long long& m, double v) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v) & 0x7fffffffffffffffull;
+    m = b > m ? b : m;
+}
+
+// The rows of one residual pass (see residual_pass): level 0's inner arrays
+// are in address space AS0.  Bound by FP64 and address arithmetic on the
+// grids whose operands stay in L2 (five hundred cycles a row and wavefront
+// before), by HBM on the largest.  Each lane forms the flux through its
+// east and its north face; the west one is the lane below's east one (two
+// values through DPP shifts), the south one the row below's north one.  Where
+// a wavefront ends inside a row, the flux into its first cell and the state
+// beyond its last are formed once per 64 rows, lane t those of row t, and
+// handed out row by row.  A seawater face is the east face with the boundary
+// state's density, concentration and pressure difference; both boundaries'
+// terms are formed only by the wavefronts that have one.  Its own function,
+// so that its registers are not the solve kernel's.
+// kFields: the face coefficients and the norm scale formed from K and phi (5
+// FP64 loads per cell instead of 9, and three FP64 divisions), with the same
+// operations as the fields kernel's stored ones, so both variants give the
+// same bits.  Per outer iteration, with the two residual passes inlined in
+// the solve kernel (a division per cell, four fluxes and both boundaries'
+// for every cell) and here: 128x64 165 -> 150 us, 64x32 84 -> 80, 4096 solves
+// of 16x8 44 -> 38; on clusters the same within 1 %.
+template <typename T, int kMode, bool kFields, int AS0>
+__device__ __attribute__((noinline)) ResNorms residual_rows(Solve<T>& S) {
+    using GP = __attribute__((address_space(1))) double*;
+    auto arr = [](double* a) { return as_ptr<1>(uniform(a)); };
+    auto at = [](GP a, uint32_t off) { return *(GP)((__attribute__((address_space(1))) char*)a + off); };
+    Phys ph;
+    ph.rho0 = uniform(S.ph.rho0); ph.rho1 = uniform(S.ph.rho1); ph.mu = uniform(S.ph.mu); ph.g = uniform(S.ph.g);
+    ph.D = uniform(S.ph.D); ph.phi0 = 0.0; ph.k0 = 0.0; ph.q_in = 0.0; ph.T = 0.0;
+    const int nx = uniform(S.nx), ny = uniform(S.ny), half = nx >> 1;
+    const double h = uniform(S.h), tau = uniform(S.tau), drho = ph.rho1 - ph.rho0;
+    const double h2t = uniform(h * h / tau), q = uniform(S.q);
+    const GP ap = arr(S.p), ac = arr(S.c), acn = arr(S.cn), aphi = arr(S.phi), aK = arr(S.K), atx = arr(S.tx),
+             awx = arr(S.wx), aty = arr(S.ty), awy = arr(S.wy), aisc = arr(S.isc);
+    const LV<T, AS0> L0(S.lv[0]);
+    auto rho = [&](double c) { return fused(drho, c, ph.rho0); };
+    const int bs = uniform(ClusterTeam::size()), rk = ClusterTeam::rank();
     const int cw = nx < bs ? nx : bs;  // both powers of two
     const int G = bs / cw;
     const int band = (ny + G - 1) / G;
     const int lane = threadIdx.x & (kWave - 1);
     const int g = rk / cw, ci = rk - g * cw;
     const int j0 = g * band;
+    const uint32_t row8 = 8u * (uint32_t)nx;
+    unsigned long long mp = 0, mc = 0;
     for (int cx = 0; cx < nx; cx += cw) {
         const int i = cx + ci;
+        const bool hw = i > 0, he = i + 1 < nx;
+        const bool sea = __any(!he), recharge = __any(!hw);
+        // ends of the wavefront inside a row
+        const int i0 = uniform(i);
+        const bool endw = nx > kWave && i0 > 0, ende = nx > kWave && i0 + kWave < nx;
         // rows below and at the start of the band (clamped into the grid)
         const int jb = j0 < ny ? j0 : ny - 1;
         const int js = jb > 0 ? jb - 1 : jb;
-        double pS = S.p[js * nx + i], cS = S.c[js * nx + i];
-        double pP = S.p[jb * nx + i], cP = S.c[jb * nx + i];
+        const uint32_t ob = (uint32_t)(jb * nx + i) * 8u, os = (uint32_t)(js * nx + i) * 8u;
+        const double pS = at(ap, os), cS = at(ac, os);
+        double pP = at(ap, ob), cP = at(ac, ob);
         double KP = 0.0, fP = 0.0, tyS = 0.0, wyS = 0.0;
         if constexpr (kFields) {
-            KP = S.K[jb * nx + i];
-            fP = S.phi[jb * nx + i];
+            KP = at(aK, ob);
+            fP = at(aphi, ob);
             if (jb > 0) {  // the first row's south face (none at j = 0)
-                const double Ks = S.K[js * nx + i], phs = S.phi[js * nx + i];
-                const FacePair fy = face_pair(ph, Ks, KP, phs, fP);
+                const FacePair fy = face_pair(ph, at(aK, os), KP, at(aphi, os), fP);
                 tyS = fy.t;
                 wyS = fy.w;
             }
         } else {
-            tyS = S.ty[js * nx + i];
-            wyS = S.wy[js * nx + i];
+            tyS = at(aty, os);
+            wyS = at(awy, os);
         }
-        // the flux through the south face of the band's first row; every
-        // later row takes it from the row below
-        FaceFlux fs = flux_face<true>(ph, S.h, pS, pP, cS, cP, tyS, wyS);
-        for (int t = 0; t < band; ++t) {  // the same trip count in every lane (shuffles)
-            const int j = j0 + t;
-            const bool active = j < ny;
-            const int jc = active ? j : ny - 1;
-            const Nb q(i, jc, nx, ny);
-            const int idx = q.idx;
-            ResIn a;
-            a.pP = pP; a.cP = cP;
-            a.pN = S.p[q.n]; a.cN = S.c[q.n];
-            a.cnP = S.cn[idx];
-            // neighbours in x: adjacent lanes, or memory at the wavefront's ends
-            double pEm = 0.0, cEm = 0.0, pWm = 0.0, cWm = 0.0, txWm = 0.0, wxWm = 0.0;
-            double KN = 0.0, fN = 0.0;
-            if constexpr (kFields) {
-                KN = S.K[q.n];
-                fN = S.phi[q.n];
-                double KEm = 0.0, fEm = 0.0;
-                if (lane == kWave - 1) { pEm = S.p[q.e]; cEm = S.c[q.e]; KEm = S.K[q.e]; fEm = S.phi[q.e]; }
-                if (lane == 0) { pWm = S.p[q.w]; cWm = S.c[q.w]; txWm = S.tx[q.w]; wxWm = S.wx[q.w]; }
-                const double KEs = __shfl_down(KP, 1, kWave), fEs = __shfl_down(fP, 1, kWave);
-                const double KE = lane == kWave - 1 ? KEm : KEs, fE = lane == kWave - 1 ? fEm : fEs;
-                a.phiP = fP;
-                const FacePair fx = face_pair(ph, KP, q.he ? KE : KP, fP, q.he ? fE : fP);
-                const FacePair fy = face_pair(ph, KP, KN, fP, fN);
-                a.txP = q.he ? fx.t : 2.0 * fx.t;
-                a.wxP = q.he ? fx.w : 2.0 * fx.w;
-                a.tyP = q.hn ? fy.t : 0.0;
-                a.wyP = q.hn ? fy.w : 0.0;
-                a.sc = res_scale(ph, S.tau, S.h, fP);
-            } else {
-                a.phiP = S.phi[idx];
-                a.txP = S.tx[idx]; a.wxP = S.wx[idx]; a.tyP = S.ty[idx]; a.wyP = S.wy[idx];
-                a.sc = S.isc[idx];
-                if (lane == kWave - 1) { pEm = S.p[q.e]; cEm = S.c[q.e]; }
-                if (lane == 0) { pWm = S.p[q.w]; cWm = S.c[q.w]; txWm = S.tx[q.w]; wxWm = S.wx[q.w]; }
+        double rP = rho(cP);
+        // the flux through the south face of the band's first row
+        const FaceFlux f0 = face_flux<true>(ph, h, rho(cS), rP, pS, pP, cS, cP, tyS, wyS);
+        double sM = f0.M, sF = f0.F;
+        for (int tb = 0; tb < band; tb += kWave) {
+            double wM0 = 0.0, wF0 = 0.0, pE0 = 0.0, cE0 = 0.0, KE0 = 0.0, fE0 = 0.0;
+            const int je = min(j0 + tb + lane, ny - 1);
+            if (endw) {
+                const uint32_t o = (uint32_t)(je * nx + i0) * 8u;
+                const double p0 = at(ap, o - 8u), p1 = at(ap, o), c0 = at(ac, o - 8u), c1 = at(ac, o);
+                const FaceFlux f = face_flux<false>(ph, h, rho(c0), rho(c1), p0, p1, c0, c1, at(atx, o - 8u), at(awx, o - 8u));
+                wM0 = f.M;
+                wF0 = f.F;
             }
-            const double pEs = __shfl_down(pP, 1, kWave), cEs = __shfl_down(cP, 1, kWave);
-            const double pWs = __shfl_up(pP, 1, kWave), cWs = __shfl_up(cP, 1, kWave);
-            const double txWs = __shfl_up(a.txP, 1, kWave), wxWs = __shfl_up(a.wxP, 1, kWave);
-            a.pE = lane == kWave - 1 ? pEm : pEs;
-            a.cE = lane == kWave - 1 ? cEm : cEs;
-            a.pW = lane == 0 ? pWm : pWs;
-            a.cW = lane == 0 ? cWm : cWs;
-            a.txW = lane == 0 ? txWm : txWs;
-            a.wxW = lane == 0 ? wxWm : wxWs;
-            FaceFlux fn = fs;
-            if (active) res_cell(ph, S, mode, idx, j, q, a, fs, fn, mp, mc);
-            // carry up one row
-            fs = fn;
-            pP = a.pN; cP = a.cN;
-            KP = KN; fP = fN;
+            if (ende) {
+                const uint32_t o = (uint32_t)(je * nx + i0 + kWave) * 8u;
+                pE0 = at(ap, o);
+                cE0 = at(ac, o);
+                if constexpr (kFields) {
+                    KE0 = at(aK, o);
+                    fE0 = at(aphi, o);
+                }
+            }
+            const int tn = min(kWave, band - tb);
+            for (int t = 0; t < tn; ++t) {  // the same trip count in every lane (shifts)
+                const int j = j0 + tb + t;
+                const bool active = j < ny;
+                const int jc = active ? j : ny - 1;
+                const bool hs = jc > 0, hn = jc + 1 < ny;
+                const uint32_t o = (uint32_t)(jc * nx + i) * 8u, on = hn ? o + row8 : o;
+                const double pN = at(ap, on), cN = at(ac, on), cn = at(acn, o);
+                double KN = 0.0, fN = 0.0, phiP, tx, wx, ty, wy, sc;
+                if constexpr (kFields) {
+                    KN = at(aK, on);
+                    fN = at(aphi, on);
+                    phiP = fP;
+                    const double KE = wave_above(KP, lane_value(KE0, t)), fE = wave_above(fP, lane_value(fE0, t));
+                    const FacePair fx = face_pair(ph, KP, he ? KE : KP, fP, he ? fE : fP);
+                    const FacePair fy = face_pair(ph, KP, KN, fP, fN);
+                    tx = he ? fx.t : 2.0 * fx.t;
+                    wx = he ? fx.w : 2.0 * fx.w;
+                    ty = hn ? fy.t : 0.0;
+                    wy = hn ? fy.w : 0.0;
+                    sc = res_scale(ph, tau, h, fP);
+                } else {
+                    phiP = at(aphi, o);
+                    tx = at(atx, o); wx = at(awx, o); ty = at(aty, o); wy = at(awy, o);
+                    sc = at(aisc, o);
+                }
+                // east face: interior, or the seawater boundary at half a
+                // cell's distance (p_B = -rho1 g y, c_B = 1)
+                double cE = wave_above(cP, ende ? lane_value(cE0, t) : 0.0);
+                double dE = wave_above(pP, ende ? lane_value(pE0, t) : 0.0) - pP;
+                double rE = rho(cE);
+                if (sea) {
+                    const double y = fused(jc + 0.5, h, -1.0);
+                    const double dB = fused(-ph.rho1 * ph.g, y, -pP);
+                    cE = he ? cE : 1.0;
+                    rE = he ? rE : ph.rho1;
+                    dE = he ? dE : dB;
+                }
+                const FaceFlux fe = face_flux(0.5 * (rP + rE), dE, cP, cE, tx, wx);
+                // west face: out of the west neighbour, or the recharge
+                double wM = wave_below(fe.M, endw ? lane_value(wM0, t) : 0.0);
+                double wF = wave_below(fe.F, endw ? lane_value(wF0, t) : 0.0);
+                double ldif = 0.0, lM = 0.0;
+                if (recharge) {  // inflow rho0 q h of fresh water (c_B = 0)
+                    const double rB = 0.5 * (rP + ph.rho0);
+                    ldif = 2.0 * rB * phiP * ph.D;
+                    lM = -ph.rho0 * q * h;
+                    wM = hw ? wM : -lM;
+                    wF = hw ? wF : -rounded_mul(ldif, cP);
+                }
+                // north face (the top is impermeable)
+                const double rN = rho(cN);
+                const FaceFlux fn = face_flux<true>(ph, h, rP, rN, pP, pN, cP, cN, ty, wy);
+                const double st = h2t * phiP, rn = rho(cn);
+                double Rp = fused(rP - rn, st, fe.M);
+                double Rc = fused(fused(cP, rP, -rounded_mul(cn, rn)), st, fe.F);
+                Rp -= wM;
+                Rc -= wF;
+                Rp += hn ? fn.M : 0.0;
+                Rc += hn ? fn.F : 0.0;
+                Rp -= hs ? sM : 0.0;
+                Rc -= hs ? sF : 0.0;
+                if (active) {
+                    if constexpr (kMode != 2) {
+                        abs_max(mp, Rp * sc);
+                        abs_max(mc, Rc * sc);
+                    }
+                    if constexpr (kMode == 0) {
+                        const int ps = jc * nx + ((i ^ jc) & 1) * half + (i >> 1);  // pidx: colour-split
+                        L0.te[ps] = (T)fe.lam;
+                        L0.tn[ps] = (T)(hn ? fn.lam : 0.0);
+                        L0.b[ps] = (T)(-Rp);
+                        L0.x[ps] = (T)0;
+                    } else if constexpr (kMode == 1) {
+                        const int idx = jc * nx + i;
+                        L0.mx[idx] = (T)(he ? fe.M : 0.0);
+                        L0.dx[idx] = (T)(he ? fe.dif : 0.0);
+                        L0.my[idx] = (T)(hn ? fn.M : 0.0);
+                        L0.dy[idx] = (T)(hn ? fn.dif : 0.0);
+                        if (!he) { L0.dr[jc] = (T)fe.dif; L0.mr[jc] = (T)fe.M; }
+                        if (!hw) { L0.dl[jc] = (T)ldif; L0.ml[jc] = (T)(-lM); }
+                        L0.acc[idx] = (T)(st * rn);
+                        L0.b[idx] = (T)(-(Rc - cP * Rp));
+                        L0.x[idx] = (T)0;
+                    } else {
+                        S.rout_p[jc * nx + i] = Rp;
+                        S.rout_c[jc * nx + i] = Rc;
+                    }
+                }
+                // carry up one row
+                if (active) { sM = fn.M; sF = fn.F; }
+                pP = pN; cP = cN; rP = rN;
+                KP = KN; fP = fN;
+            }
         }
     }
+    return {__longlong_as_double((long long)mp), __longlong_as_double((long long)mc)};
+}
+
+template <typename T, int kMode, bool kFields>
+__device__ inline ResNorms residual_rows(Solve<T>& S) {
+    if (kMode != 2 && S.lds_from == 0) return residual_rows<T, kMode, false, 3>(S);
+    return residual_rows<T, kMode, kFields, 1>(S);
 }
 
 // mode 0: R^p and R^c, pressure coefficients te/tn at level 0, and the
 //         scaled max norms (block max).
 // mode 1: the salt defect S = R^c - c R^p with the transport coefficients
 //         at level 0.
-// mode 2: R^p and R^c into S.rout_p, S.rout_c (the residual entry point).
+// (residual_rows' mode 2: R^p and R^c into S.rout_p, S.rout_c, the residual
+// entry point.)
 // Thread layout: lanes along x (cw = min(nx, blockDim) columns), the
 // blockDim / cw row groups each march up their own band of rows.  A cell
-// takes p and c of the rows below and above from the registers of the
-// previous row and a load of the next one, and its east and west
-// neighbours' values from the adjacent lanes (one-lane loads only at the
-// ends of a wavefront): 9 full loads per cell instead of 21.  Grids of at
-// least HENRY_RES_FIELDS_NX columns form the face coefficients from K and
-// phi instead (their passes are bound by bandwidth); on smaller ones, whose
-// passes wait on load latency, the divisions would lengthen the wait.
+// takes p and c of the row below from the registers of the previous row and
+// its east and west neighbours' values from the adjacent lanes: 9 loads per
+// cell.  Grids of at least HENRY_RES_FIELDS_NX columns form the face
+// coefficients from K and phi instead (their passes are bound by bandwidth);
+// on smaller ones, whose passes wait on load latency, the divisions would
+// lengthen the wait.
 // The row bands are spread over all threads of the cluster; mode 0 ends
 // with the cluster-wide norms, mode 1 with a cluster barrier only.
 template <typename T>
-__device__ void residual_pass(const Phys& ph, Solve<T>& S, int mode, double* red, double& np_out, double& nc_out,
-                              PhaseClock* pcx = nullptr) {
-    double mp = 0.0, mc = 0.0;
-    if (HENRY_RES_FIELDS_NX > 0 && S.nx >= HENRY_RES_FIELDS_NX) residual_rows<true>(ph, S, mode, mp, mc);
-    else residual_rows<false>(ph, S, mode, mp, mc);
+__device__ inline void residual_pass(Solve<T>& S, int mode, double* red, double& np_out, double& nc_out,
+                                     PhaseClock* pcx = nullptr) {
+    constexpr bool kF = HENRY_RES_FIELDS_NX > 0;
+    ResNorms m;
+    if (kF && S.nx >= HENRY_RES_FIELDS_NX) m = mode == 0 ? residual_rows<T, 0, kF>(S) : residual_rows<T, 1, kF>(S);
+    else m = mode == 0 ? residual_rows<T, 0, false>(S) : residual_rows<T, 1, false>(S);
     if (pcx) pcx->tick(mode == 0 ? 23 : 21);
-    cluster_max2(mp, mc, red, np_out, nc_out);
+    cluster_max2(m.p, m.c, red, np_out, nc_out);
     __syncthreads();
 }
 
@@ -1989,6 +2083,185 @@ __device__ void line_smooth(Level<T>& v, bool ylines) {
 
 #include "henry_wave.hpp"
 
+// ------------------------------------------------------------------ levels in registers
+// A level of which every thread of the team holds C consecutive cells of each
+// colour (one pass: C = 1, 2 or 4) is smoothed from registers: couplings,
+// reciprocal diagonals, b and x of the thread's cells are loaded or formed
+// once per leg instead of once per half-sweep, the west and east neighbours
+// are the thread's own other colour and one value of the next lane, and a
+// half-sweep loads only the rows above and below: 48 bytes for four cells
+// instead of 160, and a fifth of the instructions.  The arithmetic per cell
+// is rbgs's and level_residual's.  LEVELTIMES
+// A row's lanes lie in one wavefront: nx <= 128 C.
+template <int C, typename T> struct VecC { using type = T __attribute__((ext_vector_type(C))); };
+template <typename T> struct VecC<1, T> { using type = T; };
+
+template <int C, typename T, int AS>
+__device__ inline void load_c(typename AsPtr<T, AS>::type p, T (&o)[C]) {
+    if constexpr (C == 1) o[0] = *p;
+    else {
+        const auto v = *(typename AsPtr<typename VecC<C, T>::type, AS>::type)p;
+#pragma unroll
+        for (int q = 0; q < C; ++q) o[q] = v[q];
+    }
+}
+template <int C, typename T, int AS>
+__device__ inline void store_c(typename AsPtr<T, AS>::type p, const T (&x)[C]) {
+    if constexpr (C == 1) *p = x[0];
+    else {
+        typename VecC<C, T>::type v;
+#pragma unroll
+        for (int q = 0; q < C; ++q) v[q] = x[q];
+        *(typename AsPtr<typename VecC<C, T>::type, AS>::type)p = v;
+    }
+}
+
+// Value of the lane below / above in the wavefront (0 at its ends).
+template <typename T> __device__ inline T wave_below(T v) { return dpp_row<0x138>(v); }  // wave_shr:1
+template <typename T> __device__ inline T wave_above(T v) { return dpp_row<0x130>(v); }  // wave_shl:1
+
+template <typename T, class Team, int AS, int C>
+struct RbOwn {
+    const LV<T, AS>& v;
+    int nx, ny, half, j, kr, o;  // o: column 2 (kr + q) + o of the red cells, 1 - o of the black ones
+    bool active;
+    T cw[2][C], ce[2][C], cs[2][C], cn[2][C], cd[2][C], dred[C], b[2][C], x[2][C];
+
+    __device__ inline RbOwn(const LV<T, AS>& lv) : v(lv) {
+        nx = v.nx; ny = v.ny; half = nx >> 1;
+        const int k = Team::rank() * C, m = half * ny;
+        active = k < m;
+        const int kk = active ? k : 0;
+        j = kk >> log2i(half);
+        kr = kk & (half - 1);
+        o = j & 1;
+        const bool hs = j > 0;
+        T te[2][C], tn[2][C], ts[2][C];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            load_c<C, T, AS>(v.te + j * nx + c * half + kr, te[c]);
+            load_c<C, T, AS>(v.tn + j * nx + c * half + kr, tn[c]);
+            load_c<C, T, AS>(v.tn + (hs ? (j - 1) * nx + (1 - c) * half + kr : j * nx + kr), ts[c]);
+            load_c<C, T, AS>(v.b + j * nx + c * half + kr, b[c]);
+        }
+        // the colour whose cells lie in the even columns of the row has its
+        // first west neighbour in the lane before
+        const T edge = wave_below(o ? te[0][C - 1] : te[1][C - 1]);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int oc = o ^ c;
+#pragma unroll
+            for (int q = 0; q < C; ++q) {
+                const bool hw = kr + q + oc > 0, he = !(oc == 1 && kr + q == half - 1);
+                const T tW = oc ? te[1 - c][q] : (q > 0 ? te[1 - c][q > 0 ? q - 1 : 0] : edge);
+                cw[c][q] = hw ? tW : (T)0;
+                ce[c][q] = he ? te[c][q] : (T)0;  // the seawater coefficient is diagonal only
+                cn[c][q] = tn[c][q];
+                cs[c][q] = hs ? ts[c][q] : (T)0;
+                const T d = te[c][q] + cw[c][q] + cn[c][q] + cs[c][q];
+                if (c == 0) dred[q] = d;
+                cd[c][q] = diag_prep(d);
+            }
+        }
+    }
+    __device__ inline void put(int c) const {
+        if (active) store_c<C, T, AS>(v.x + j * nx + c * half + kr, x[c]);
+    }
+    // the neighbours of the cells of colour c: win[q], win[q + 1] west and east
+    __device__ inline void neighbours(int c, T (&win)[C + 1], T (&xs)[C], T (&xn)[C]) const {
+        const int oc = o ^ c;
+        load_c<C, T, AS>(v.x + (j > 0 ? j - 1 : j) * nx + (1 - c) * half + kr, xs);
+        load_c<C, T, AS>(v.x + (j + 1 < ny ? j + 1 : j) * nx + (1 - c) * half + kr, xn);
+        const T below = wave_below(x[1 - c][C - 1]), above = wave_above(x[1 - c][0]);
+        win[0] = oc ? x[1 - c][0] : below;
+#pragma unroll
+        for (int q = 1; q < C; ++q) win[q] = oc ? x[1 - c][q] : x[1 - c][q - 1];
+        win[C] = oc ? above : x[1 - c][C - 1];
+    }
+    __device__ inline void half_sweep(int c) {
+        T win[C + 1], xs[C], xn[C];
+        neighbours(c, win, xs, xn);
+#pragma unroll
+        for (int q = 0; q < C; ++q) {
+            T a = b[c][q];
+            a += cw[c][q] * win[q];
+            a += ce[c][q] * win[q + 1];
+            a += cs[c][q] * xs[q];
+            a += cn[c][q] * xn[q];
+            x[c][q] = diag_div(a, cd[c][q]);
+        }
+        put(c);
+        Team::sync();
+    }
+};
+
+// Pre-smoothing (two sweeps from x = 0) and the red cells' residual.
+template <typename T, class Team, int AS, int C>
+__device__ __attribute__((noinline)) void rb_down(const Level<T>& v0) {
+    const LV<T, AS> v(v0);
+    RbOwn<T, Team, AS, C> R(v);
+#pragma unroll
+    for (int q = 0; q < C; ++q) R.x[0][q] = diag_div(R.b[0][q], R.cd[0][q]);
+    R.put(0);
+    Team::sync();
+    R.half_sweep(1);
+    R.half_sweep(0);
+    R.half_sweep(1);
+    T win[C + 1], xs[C], xn[C], r[C];
+    R.neighbours(0, win, xs, xn);
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+        T ax = fused(R.dred[q], R.x[0][q], -rounded_mul(R.cw[0][q], win[q]));
+        ax -= R.ce[0][q] * win[q + 1];
+        ax -= R.cs[0][q] * xs[q];
+        ax -= R.cn[0][q] * xn[q];
+        r[q] = R.b[0][q] - ax;
+    }
+    if (R.active) store_c<C, T, AS>(v.r + R.j * R.nx + R.kr, r);
+    Team::sync();
+}
+
+// Prolongation from level c and the post-smoothing (two sweeps).
+template <typename T, class Team, int ASC, int AS, int C>
+__device__ __attribute__((noinline)) void rb_up(const Level<T>& c0, const Level<T>& v0) {
+    const LV<T, ASC> c(c0);
+    const LV<T, AS> v(v0);
+    RbOwn<T, Team, AS, C> R(v);
+    const int j = R.j, kr = R.kr, half = R.half, hc = half >> 1;
+    // coarse cells kr - 1 .. kr + C of the rows J and Jn
+    const int J = j >> 1, Jn = (j & 1) ? min(J + 1, c.ny - 1) : max(J - 1, 0);
+    T cj[C + 2], cn[C + 2];
+#pragma unroll
+    for (int q = 0; q < C + 2; ++q) {
+        const int I = min(max(kr - 1 + q, 0), half - 1);
+        cj[q] = c.x[J * half + ((I + J) & 1) * hc + (I >> 1)];
+        cn[q] = c.x[Jn * half + ((I + Jn) & 1) * hc + (I >> 1)];
+    }
+#pragma unroll
+    for (int col = 0; col < 2; ++col) {
+        load_c<C, T, AS>(v.x + j * R.nx + col * half + kr, R.x[col]);
+        const int oc = R.o ^ col;
+#pragma unroll
+        for (int q = 0; q < C; ++q)
+            R.x[col][q] = R.x[col][q] + prolonged(cj[q + 1], oc ? cj[q + 2] : cj[q], cn[q + 1], oc ? cn[q + 2] : cn[q]);
+        R.put(col);
+    }
+    Team::sync();
+    for (int s = 0; s < 2; ++s) {
+        R.half_sweep(0);
+        R.half_sweep(1);
+    }
+}
+
+// Cells of one colour per thread when the level takes one such pass of the
+// team (0: it does not, or its rows cross wavefronts).
+template <class Team>
+__device__ inline int rb_cells(int nx, int ny) {
+    const int m = (nx >> 1) * ny, ts = Team::size();
+    const int c = m <= ts ? 1 : m <= 2 * ts ? 2 : m <= 4 * ts ? 4 : 0;
+    return nx <= 128 * c ? c : 0;
+}
+
 // ------------------------------------------------------------------ V-cycles
 // Downward leg on level l (address space AS; level l+1 in ASN): smooth,
 // residual, restriction to level l+1.
@@ -1996,10 +2269,21 @@ template <typename T, bool kTransport, bool kTrans, class Team, int AS, int ASN>
 __device__ void vdown(Solve<T>& S, int l) {
     Level<T>& v = S.lv[l];
     Level<T>& c = (S.hand && l + 1 == S.lc) ? S.hg : S.lv[l + 1];
-    if constexpr (kTransport) line_smooth<T, kTrans, Team, AS>(v, false);
-    else rbgs<T, Team, AS>(v, 2);
-    level_residual<T, kTransport, kTrans, Team, AS>(v);
-    Team::sync();
+    if constexpr (kTransport) {
+        line_smooth<T, kTrans, Team, AS>(v, false);
+        level_residual<T, kTransport, kTrans, Team, AS>(v);
+        Team::sync();
+    } else {
+        switch (rb_cells<Team>(v.nx, v.ny)) {
+            case 1: rb_down<T, Team, AS, 1>(v); break;
+            case 2: rb_down<T, Team, AS, 2>(v); break;
+            case 4: rb_down<T, Team, AS, 4>(v); break;
+            default:
+                rbgs<T, Team, AS>(v, 2);
+                level_residual<T, kTransport, kTrans, Team, AS>(v);
+                Team::sync();
+        }
+    }
     restrict_residual<T, Team, AS, ASN, !kTransport>(v, c);
     Team::sync();
 }
@@ -2014,6 +2298,13 @@ template <typename T, bool kTransport, bool kTrans, class Team, int AS, int ASN>
 __device__ void vup(Solve<T>& S, int l) {
     Level<T>& v = S.lv[l];
     const Level<T>& c = (S.hand && l + 1 == S.lc) ? S.hg : S.lv[l + 1];
+    if constexpr (!kTransport) {
+        switch (rb_cells<Team>(v.nx, v.ny)) {
+            case 1: return rb_up<T, Team, ASN, AS, 1>(c, v);
+            case 2: return rb_up<T, Team, ASN, AS, 2>(c, v);
+            case 4: return rb_up<T, Team, ASN, AS, 4>(c, v);
+        }
+    }
     prolong_add<T, Team, ASN, AS, !kTransport>(c, v);
     Team::sync();
     if constexpr (kTransport) line_smooth<T, kTrans, Team, AS>(v, false);
@@ -2185,7 +2476,7 @@ __device__ int implicit_step(const Phys& ph, Solve<T>& S, double* red, int max_o
     for (int it = 0; it < max_outer; ++it) {
         double np, nc;
         pc.tick(13);
-        residual_pass(ph, S, 0, red, np, nc, &pc);
+        residual_pass(S, 0, red, np, nc, &pc);
         pc.tick(0);
         if (!(np == np) || !(nc == nc) || np > 1e300 || nc > 1e300) return 2;
         if (np <= tol && nc <= tol) return 0;
@@ -2205,7 +2496,7 @@ __device__ int implicit_step(const Phys& ph, Solve<T>& S, double* red, int max_o
         pc.tick(15);
         // the salt system's pass evaluates both residuals at the updated
         // state: the step may end here, before the salt cycle
-        residual_pass(ph, S, 1, red, np, nc, &pc);
+        residual_pass(S, 1, red, np, nc, &pc);
         if (!(np == np) || !(nc == nc) || np > 1e300 || nc > 1e300) return 2;
         if (np <= tol && nc <= tol) return 0;
         pc.tick(3);
@@ -2344,6 +2635,7 @@ __global__ void __launch_bounds__(sizeof(T) == 4 ? HENRY_FP32_THREADS : 512) hen
         bind_solve(S, lp.ws + d.ws_off, d.nx, d.ny, lds_levels, lp.lds_cells, lp.lds_block_cells);
         S.nsteps = d.nsteps;
         S.tau = ph.T / d.nsteps;
+        S.ph = ph;
         set_cluster_levels(S, lp.cluster);
     }
     __syncthreads();
@@ -2451,6 +2743,7 @@ __global__ void __launch_bounds__(1024) henry_residual_kernel(Launch lp, const d
         bind_solve(S, lp.ws + d.ws_off, d.nx, d.ny, lds_levels, 0, 0);
         S.nsteps = d.nsteps;
         S.tau = ph.T / d.nsteps;
+        S.ph = ph;
         S.q = S.scratch[0];
         S.rout_p = rp + d.field_off;
         S.rout_c = rc + d.field_off;
@@ -2462,8 +2755,7 @@ __global__ void __launch_bounds__(1024) henry_residual_kernel(Launch lp, const d
         S.cn[idx] = cn[d.field_off + idx];
     }
     __syncthreads();
-    double np, nc;
-    residual_pass(ph, S, 2, red, np, nc);
+    residual_rows<float, 2, false>(S);
 }
 
 // ------------------------------------------------------------------ random fields

@@ -16,7 +16,8 @@
 //
 // The sweeps, line solves and transfers and the order of their arithmetic
 // are those of the larger levels (rbgs, line_sweep_m with two rows per lane,
-// restrict_residual, prolong_add): bitwise the same results as when these
+// restrict_residual -- whose products are rounded before they are added, as
+// a select stands between them there --, prolong_add): bitwise the same results as when these
 // levels ran through them.  FP32, per cycle on one hierarchy (device wall
 // clock), with the generic loops before and here:
 //   32x16 and below  pressure 20.0 -> 6.1 us, transport 23.4 -> 6.7 us
@@ -33,42 +34,6 @@ __device__ inline void wave_zero(LdsPtr<T> p) {
         const int at = k + wave_lane();
         if (k + kWave <= kElems / 4 || at < kElems / 4) ((typename AsPtr<Vec4<T>, 3>::type)p)[at] = z;
     }
-}
-
-// Weights of restrict_residual along one direction: the fine cells 2I-1 and
-// 2I+2 have 1/4, 2I and 2I+1 have 3/4, with the boundary's share added.
-// Its products are rounded before they are added (there a select stands
-// between them); so here.
-template <typename T>
-__device__ inline T rounded_mul(T a, T b) {
-#pragma clang fp contract(off)
-    const T p = a * b;
-    return p;
-}
-
-// Where a sum of two products could be fused either way, the choice of the
-// larger levels' code is written out, so that a level's place does not
-// change its rounding.
-__device__ inline float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ inline double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
-// Bilinear prolongation weights 9/16, 3/16, 3/16, 1/16 (prolong_add's).
-template <typename T>
-__device__ inline T prolonged(T near, T side, T up, T far) {
-    return fused((T)0.0625, far, fused((T)0.5625, near, rounded_mul((T)0.1875, side + up)));
-}
-
-// Diagonal as the smoother divides by it: its reciprocal for float (qdiv's),
-// itself for double.
-template <typename T>
-__device__ inline T diag_prep(T d) {
-    if constexpr (sizeof(T) == 4) return __builtin_amdgcn_rcpf(d);
-    else return d;
-}
-template <typename T>
-__device__ inline T diag_div(T a, T prep) {
-    if constexpr (sizeof(T) == 4) return rounded_mul(a, prep);  // not fused into what it is added to next
-    else return a / prep;
 }
 
 // ------------------------------------------------------------------ pressure

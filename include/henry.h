@@ -121,9 +121,12 @@ typedef struct {
                                  stream instead of concurrently                  */
     int32_t cluster;          /* workgroups (CUs) sharing one solve of
                                  henry_solve_batch or henry_adjoint_batch: 1, 2,
-                                 4 or 8; 0 = built-in choice (one per 8192 fine
-                                 cells, at most 8, and at most 256 workgroups
-                                 per grid group).  Grids of 2048 cells or fewer
+                                 4 or 8; 0 = built-in choice (at most 8 and at
+                                 most 256 workgroups per grid group: one per
+                                 2048 fine cells for the batch's costliest grid
+                                 above 2048 cells -- within 128 workgroups when
+                                 the batch has other grids --, one per 8192 for
+                                 the others).  Grids of 2048 cells or fewer
                                  always use 1.  The fine levels are split over
                                  the cluster, the coarse ones run on its first
                                  workgroup; results are bitwise the same for
@@ -374,7 +377,9 @@ int henry_level_smooth(henry_ctx* ctx, int32_t nx, int32_t ny, int32_t kind, int
  * (the batch plan of the ensemble: how the solves of one grid are packed
  * onto workgroups and streams, priced by their cost n_l r_l, eq:workpl):
  *   threads  workgroup size when opts->threads == 0; 0 = built-in (128
- *            threads up to 128 cells, 256 up to 512, 512 up to 2048, above
+ *            threads up to 128 cells, 256 up to 512, 512 up to 2048 -- half
+ *            of these for more than 512 solves (256 adjoints) of one
+ *            grid --, above
  *            that 1024 with PREC_MIXED and 512 with PREC_FP64; 512 for a
  *            PREC_MIXED group whose solves are shared by clusters, which then
  *            runs the kernel's 512-thread build);
@@ -389,7 +394,8 @@ int henry_level_smooth(henry_ctx* ctx, int32_t nx, int32_t ny, int32_t kind, int
  * choices changes a result (bitwise).  The measuring driver that fills it
  * times candidates on short runs of the caller's own batch (Python
  * binding: paper_2302_07804_amd.autotune).  henry_tune_get returns the
- * effective workgroup size of a group of one workgroup per solve and the
+ * workgroup size of a group of one workgroup per solve (of up to 512
+ * solves, where it is the built-in one) and the
  * stored cluster and stream (0 / -1 = built-in); cluster and stream may be
  * NULL. */
 int henry_tune_set(henry_ctx* ctx, int32_t nx, int32_t prec, int32_t threads, int32_t cluster, int32_t stream);

@@ -225,15 +225,24 @@ int check_opts(const henry_opts_t* o) {
 }
 
 // Workgroups per solve.  A cluster needs the level below the finest in
-// global memory (more than 4 x kLdsCells cells).  Built-in choice: one
-// workgroup per 8192 fine cells, at most 8, and at most as many as keep the
-// group's clusters within the 256 CUs (one 1024-thread workgroup each).
-int cluster_size(int nx, int ny, int nsolves, int requested) {
+// global memory (more than 4 x kLdsCells cells).  Built-in choice, at most 8:
+//  - the batch's costliest grid of that size (`lead`): one workgroup per 2048
+//    fine cells, as long as its workgroups leave half the 256 CUs to the
+//    batch's other groups, or take all of them when there are none.  ms of
+//    8 to 40 steps with 1, 2, 4, 8 per solve: 16 solves of 128x64 54, 48, 43,
+//    44; 64 of them 60, 59, 56, -; 16 of 256x128 212, 165, 116, 91; 64 of
+//    them 244, 195, 142, -.  L = 4 batch with 4 and 8 per 256x128 solve: 342
+//    and 264; a L = 3 batch with 1, 2, 4 per 128x64 solve (64 of them): 120,
+//    101, 113.
+//  - other grids, which would run after it on the cluster stream: one per
+//    8192 (L = 4 batch with 2 per 128x64 solve too: 385 ms).
+int cluster_size(int nx, int ny, int nsolves, int requested, bool lead, bool alone) {
     const int cells = nx * ny;
     if (cells <= 4 * kLdsCells) return 1;
     if (requested > 0) return requested;
+    const int per = lead ? 2048 : 8192, most = lead && !alone ? 128 : 256;
     int k = 1;
-    while (2 * k <= henry::kMaxCluster && cells >= 2 * k * 8192 && 2 * k * nsolves <= 256) k *= 2;
+    while (2 * k <= henry::kMaxCluster && cells >= 2 * k * per && 2 * k * nsolves <= most) k *= 2;
     return k;
 }
 
@@ -241,15 +250,36 @@ int64_t solve_bytes(int nx, int ny, int prec) {
     return prec == HENRY_PREC_MIXED ? henry::solve_bytes<float>(nx, ny) : henry::solve_bytes<double>(nx, ny);
 }
 
-// Built-in workgroup size (the choices the measuring autotuner makes on the
-// MLMC hierarchy): twice the cells up to 512 threads, then the largest size
-// the precision's kernel is built for.
+// Built-in workgroup size: twice the cells up to 512 threads, then the
+// largest size the precision's kernel is built for.
 int default_threads(int nx, int ny, int prec) {
     const int cells = nx * ny;
     if (cells <= 128) return 128;
     if (cells <= 512) return 256;
     if (cells <= 2048) return 512;
     return max_threads(prec);
+}
+
+// The same for a group of more than `many` solves of up to 2048 cells: half
+// of it, so that twice as many solves share a CU (a solve's waits are then
+// others' work).  ms at the built-in size and at half of it: 16x8, 256 solves
+// 4.7 and 4.9, 1024 6.3 and 5.9, 4096 17.1 and 12.4; 32x16, 256 solves 6.9 and
+// 7.1, 1280 17.6 and 11.2; 64x32, 512 solves 23.4 and 23.5, 1024 45.8 and
+// 43.2: 512.  The adjoint kernel's 256 registers let one workgroup of 512
+// threads onto a CU: 256 (32x16, 256 solves 22.1 and 23.4, 1024 53 and 34;
+// 64x32, 512 solves 104 and 78).
+constexpr int kManySolves = 512, kManyAdjoints = 256;
+int group_threads(int nx, int ny, int nsolves, int prec, int many) {
+    const int t = default_threads(nx, ny, prec);
+    return nsolves > many && nx * ny <= 2048 ? t / 2 : t;
+}
+
+// Index of the group that `lead` means in cluster_size: the first, in cost
+// order, of more than 4 x kLdsCells cells.
+int lead_group(const std::vector<Group>& order) {
+    for (size_t gi = 0; gi < order.size(); ++gi)
+        if (order[gi].nx * order[gi].ny > 4 * kLdsCells) return (int)gi;
+    return -1;
 }
 
 int64_t desc_bytes(int nsolves) { return henry::align256((int64_t)nsolves * (int64_t)sizeof(henry::SolveDesc)); }
@@ -680,15 +710,18 @@ int solve_batch_impl(henry_ctx* ctx, const henry_grid_t* solves, int32_t nsolves
     std::vector<henry::SolveDesc> table;
     table.reserve(nsolves);
     std::vector<int> gstart;
+    const int lead = lead_group(order);
     for (auto& G : order) {
         gstart.push_back((int)table.size());
         for (int k : G.members) table.push_back(desc[k]);
         const auto it = ctx->tuned.find((long)G.nx * 4 + prec);
         const Tuned tu = it != ctx->tuned.end() ? it->second : Tuned{};
+        const int nb = (int)G.members.size();
         int t = o->threads;
-        G.cluster = cluster_size(G.nx, G.ny, (int)G.members.size(), o->cluster > 0 ? o->cluster : tu.cluster);
+        G.cluster = cluster_size(G.nx, G.ny, nb, o->cluster > 0 ? o->cluster : tu.cluster, lead >= 0 && &G == &order[lead],
+                                 order.size() == 1);
         if (t == 0 && tu.threads > 0) t = tu.threads;
-        if (t == 0) t = (prec == HENRY_PREC_MIXED && G.cluster > 1) ? 512 : default_threads(G.nx, G.ny, prec);
+        if (t == 0) t = (prec == HENRY_PREC_MIXED && G.cluster > 1) ? 512 : group_threads(G.nx, G.ny, nb, prec, kManySolves);
         G.threads = t;
         G.stream = tu.stream;
     }
@@ -1031,6 +1064,7 @@ int henry_adjoint_batch(henry_ctx* ctx, const henry_grid_t* solves, int32_t nsol
     std::vector<Group> order;
     for (auto& kv : groups) order.push_back(kv.second);
     std::sort(order.begin(), order.end(), [](const Group& a, const Group& b) { return a.cost > b.cost; });
+    const int lead = lead_group(order);
     std::vector<henry::SolveDesc> table;
     std::vector<int> gstart;
     for (auto& G : order) {
@@ -1039,9 +1073,11 @@ int henry_adjoint_batch(henry_ctx* ctx, const henry_grid_t* solves, int32_t nsol
         const auto it = ctx->tuned.find((long)G.nx * 4 + prec);
         const Tuned tu = it != ctx->tuned.end() ? it->second : Tuned{};
         int t = o->threads;
-        if (t == 0) t = tu.threads > 0 ? tu.threads : default_threads(G.nx, G.ny, prec);
+        if (t == 0)
+            t = tu.threads > 0 ? tu.threads : group_threads(G.nx, G.ny, (int)G.members.size(), prec, kManyAdjoints);
         G.threads = std::min(t, kAdjMaxThreads);
-        G.cluster = cluster_size(G.nx, G.ny, (int)G.members.size(), o->cluster > 0 ? o->cluster : tu.cluster);
+        G.cluster = cluster_size(G.nx, G.ny, (int)G.members.size(), o->cluster > 0 ? o->cluster : tu.cluster,
+                                 lead >= 0 && &G == &order[lead], order.size() == 1);
         G.stream = tu.stream;
     }
     DeviceGuard dg(ctx->device);

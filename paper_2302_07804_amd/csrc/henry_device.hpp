@@ -1995,10 +1995,56 @@ struct Segment {
     Vec4<T> x;
 };
 
+// What the rows beside a line hold: zero, v.x, or (first colour after the
+// coarse levels) v.x and the correction prolonged from level c.
+struct BesideZero {
+    template <class L, typename T>
+    __device__ inline void operator()(const L&, int, int, int, int, T&, T&) const {}
+};
+struct BesideX {
+    template <typename T, int AS>
+    __device__ inline void operator()(const LV<T, AS>& v, int, int, int ks, int kn, Vec4<T>& xS, Vec4<T>& xN) const {
+        xS = *(typename AsPtr<Vec4<T>, AS>::type)(v.x + ks);
+        xN = *(typename AsPtr<Vec4<T>, AS>::type)(v.x + kn);
+    }
+};
+template <typename T, int TL, int ASC>
+struct BesideProlonged {
+    const LV<T, ASC>& c;
+    // a line of an even row 2J: the rows beside it are the upper ones of
+    // coarse rows J - 1 and J
+    template <int AS>
+    __device__ inline void operator()(const LV<T, AS>& v, int lane, int j, int ks, int kn, Vec4<T>& xS, Vec4<T>& xN) const {
+        using LL = LineLanes<TL>;
+        using V2 = T __attribute__((ext_vector_type(2)));
+        constexpr int nc = 2 * TL;
+        const int t = LL::segment(lane), J = j >> 1;
+        T cc[3][4];  // coarse cells 2t - 1 .. 2t + 2 of rows J - 1, J, J + 1
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const int Jr = min(max(J + r - 1, 0), c.ny - 1);
+            const V2 o = *(typename AsPtr<V2, ASC>::type)(c.x + Jr * nc + 2 * t);
+            const T w = LL::template below<1>((T)o[1], lane), e = LL::template above<1>((T)o[0], lane);
+            cc[r][0] = t > 0 ? w : (T)o[0];
+            cc[r][1] = o[0];
+            cc[r][2] = o[1];
+            cc[r][3] = t < TL - 1 ? e : (T)o[1];
+        }
+        BesideX{}(v, lane, j, ks, kn, xS, xN);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int m = 1 + (q >> 1), w = (q & 1) ? m + 1 : m - 1;
+            xS[q] = xS[q] + prolonged(cc[0][m], cc[0][w], cc[1][m], cc[1][w]);
+            xN[q] = xN[q] + prolonged(cc[1][m], cc[1][w], cc[2][m], cc[2][w]);
+        }
+    }
+};
+
 // Solves this wavefront's lines of colour col from line (base + rank) / TL
-// on; with kZero the rows beside them are still zero.
-template <typename T, bool kTrans, int TL, class Team, int AS, bool kZero>
-__device__ inline void line_solve_x(const LV<T, AS>& v, int col, int base, Segment<T>& g) {
+// on.
+template <typename T, bool kTrans, int TL, class Team, int AS, class Beside>
+__device__ inline void line_solve_x(const LV<T, AS>& v, int col, int base, Segment<T>& g, const Beside& beside) {
+    constexpr bool kZero = std::is_same<Beside, BesideZero>::value;
     using LL = LineLanes<TL>;
     using V4 = Vec4<T>;
     constexpr int MS = 4, nx = MS * TL;
@@ -2018,10 +2064,7 @@ __device__ inline void line_solve_x(const LV<T, AS>& v, int col, int base, Segme
     const V4 acc = load4(v.acc + k0), mE = load4(v.mx + k0), dE = load4(v.dx + k0), mN = load4(v.my + k0),
              dN = load4(v.dy + k0), mS = load4(v.my + ks), dS = load4(v.dy + ks), bq = load4(v.b + k0);
     V4 xS = {}, xN = {};
-    if constexpr (!kZero) {
-        xS = load4(v.x + ks);
-        xN = load4(v.x + kn);
-    }
+    beside(v, lane, j, ks, kn, xS, xN);
     const T bE = pos(-v.mr[j]) + v.dr[j], bW = v.dl[j] + v.ml[j];
     const T mW0 = LL::template below<1>((T)mE[3], lane), dW0 = LL::template below<1>((T)dE[3], lane);
     T cp[MS], y[MS], u[MS];
@@ -2097,7 +2140,29 @@ __device__ __attribute__((noinline)) void line_sweep_x(Level<T>& v0, int col) {
     const int need = ((v.ny - col + 1) >> 1) * TL;
     for (int base = 0; base < need; base += Team::size()) {
         Segment<T> g;
-        line_solve_x<T, kTrans, TL, Team, AS, false>(v, col, base, g);
+        line_solve_x<T, kTrans, TL, Team, AS>(v, col, base, g, BesideX{});
+    }
+    Team::sync();
+}
+
+// Prolongation from level c and the post-smoothing.  A line replaces its row,
+// so only the odd rows, as the first colour's neighbours, are ever read with
+// the correction: the even rows' lines add it to what they load, and a pass
+// over the level with its barrier is gone.  Per iteration, level 0 from the
+// prolongation on: 64x32 9.2 -> 4.9 us, 128x64 in one workgroup 10.6 -> 7.0,
+// 256x128 on 8 workgroups 11.9 -> 8.1 (level 1 14.3 -> 11.1).
+template <typename T, bool kTrans, int TL, class Team, int ASC, int AS>
+__device__ __attribute__((noinline)) void line_up(const Level<T>& c0, Level<T>& v0) {
+    const LV<T, ASC> c(c0);
+    const LV<T, AS> v(v0);
+    for (int base = 0; base < (v.ny >> 1) * TL; base += Team::size()) {
+        Segment<T> g;
+        line_solve_x<T, kTrans, TL, Team, AS>(v, 0, base, g, BesideProlonged<T, TL, ASC>{c});
+    }
+    Team::sync();
+    for (int base = 0; base < (v.ny >> 1) * TL; base += Team::size()) {
+        Segment<T> g;
+        line_solve_x<T, kTrans, TL, Team, AS>(v, 1, base, g, BesideX{});
     }
     Team::sync();
 }
@@ -2116,11 +2181,11 @@ __device__ __attribute__((noinline)) void line_down(Level<T>& v0) {
     const LV<T, AS> v(v0);
     const int lane = threadIdx.x & (kWave - 1);
     Segment<T> g;
-    line_solve_x<T, kTrans, TL, Team, AS, true>(v, 0, 0, g);
+    line_solve_x<T, kTrans, TL, Team, AS>(v, 0, 0, g, BesideZero{});
     Team::sync();
     {
         Segment<T> o;
-        line_solve_x<T, kTrans, TL, Team, AS, false>(v, 1, 0, o);
+        line_solve_x<T, kTrans, TL, Team, AS>(v, 1, 0, o, BesideX{});
     }
     Team::sync();
     const int ks = g.j > 0 ? g.k0 - nx : g.k0, kn = g.j + 1 < v.ny ? g.k0 + nx : g.k0;
@@ -2188,9 +2253,9 @@ __device__ void line_smooth(Level<T>& v, bool ylines) {
 // half-sweep loads only the rows above and below: 48 bytes for four cells
 // instead of 160, and a fifth of the instructions.  The arithmetic per cell
 // is rbgs's and level_residual's.  Pressure legs of level 0 per iteration,
-// down and up: 128x64 in one workgroup 17.5 and 13.0 -> 11.4 and 5.2 us,
-// 64x32 9.6 and 7.6 -> 5.7 and 3.3, 256x128 on 8 workgroups 15.3 and 13.6 ->
-// 11.9 and 9.5.
+// down and up: 128x64 in one workgroup 17.5 and 13.0 -> 11.4 and 4.7 us,
+// 64x32 9.6 and 7.6 -> 5.7 and 2.9, 256x128 on 8 workgroups 15.3 and 13.6 ->
+// 11.9 and 9.4.
 // A row's lanes lie in one wavefront: nx <= 128 C.
 template <int C, typename T> struct VecC { using type = T __attribute__((ext_vector_type(C))); };
 template <typename T> struct VecC<1, T> { using type = T; };
@@ -2320,7 +2385,12 @@ __device__ __attribute__((noinline)) void rb_down(const Level<T>& v0) {
     Team::sync();
 }
 
-// Prolongation from level c and the post-smoothing (two sweeps).
+// Prolongation from level c and the post-smoothing (two sweeps).  A half-sweep
+// replaces the cells of its colour, so only the black cells, as the first
+// red half-sweep's neighbours, are ever read with the correction.  (Each
+// thread adding it to the black cells it loads, without the pass that stores
+// them, was no faster: 64x32 3.3 -> 3.7 us a leg, 128x64 in one workgroup
+// 5.2 -> 7.9.)
 template <typename T, class Team, int ASC, int AS, int C>
 __device__ __attribute__((noinline)) void rb_up(const Level<T>& c0, const Level<T>& v0) {
     const LV<T, ASC> c(c0);
@@ -2336,15 +2406,12 @@ __device__ __attribute__((noinline)) void rb_up(const Level<T>& c0, const Level<
         cj[q] = c.x[J * half + ((I + J) & 1) * hc + (I >> 1)];
         cn[q] = c.x[Jn * half + ((I + Jn) & 1) * hc + (I >> 1)];
     }
+    load_c<C, T, AS>(v.x + j * R.nx + half + kr, R.x[1]);
 #pragma unroll
-    for (int col = 0; col < 2; ++col) {
-        load_c<C, T, AS>(v.x + j * R.nx + col * half + kr, R.x[col]);
-        const int oc = R.o ^ col;
-#pragma unroll
-        for (int q = 0; q < C; ++q)
-            R.x[col][q] = R.x[col][q] + prolonged(cj[q + 1], oc ? cj[q + 2] : cj[q], cn[q + 1], oc ? cn[q + 2] : cn[q]);
-        R.put(col);
-    }
+    for (int q = 0; q < C; ++q)
+        R.x[1][q] = R.x[1][q] + (R.o ? prolonged(cj[q + 1], cj[q], cn[q + 1], cn[q])
+                                     : prolonged(cj[q + 1], cj[q + 2], cn[q + 1], cn[q + 2]));
+    R.put(1);
     Team::sync();
     for (int s = 0; s < 2; ++s) {
         R.half_sweep(0);
@@ -2403,7 +2470,13 @@ template <typename T, bool kTransport, bool kTrans, class Team, int AS, int ASN>
 __device__ void vup(Solve<T>& S, int l) {
     Level<T>& v = S.lv[l];
     const Level<T>& c = (S.hand && l + 1 == S.lc) ? S.hg : S.lv[l + 1];
-    if constexpr (!kTransport) {
+    if constexpr (kTransport) {
+        switch (v.nx) {
+            case 64: return line_up<T, kTrans, 16, Team, ASN, AS>(c, v);
+            case 128: return line_up<T, kTrans, 32, Team, ASN, AS>(c, v);
+            case 256: return line_up<T, kTrans, 64, Team, ASN, AS>(c, v);
+        }
+    } else {
         switch (rb_cells<Team>(v.nx, v.ny)) {
             case 1: return rb_up<T, Team, ASN, AS, 1>(c, v);
             case 2: return rb_up<T, Team, ASN, AS, 2>(c, v);

@@ -73,6 +73,8 @@ namespace HENRY_NS {
 // gathers before it writes any, so that their loads are in flight together;
 // the 1024-thread build has no registers to spare for more than one.
 constexpr int kTBatch = HENRY_FP32_THREADS <= 512 ? HENRY_TRANSFER_BATCH : 1;
+// strips of eight cells per thread take more registers than the 1024-thread build has
+constexpr bool kStripWide = HENRY_FP32_THREADS <= 512;
 
 constexpr int kMaxLevels = 12;  // ny <= 512 -> at most 10 multigrid levels
 constexpr int kWave = 64;
@@ -590,6 +592,7 @@ struct ClusterState {
     uint64_t wait;   // bound of one wait (wall-clock ticks)
     uint8_t* stage;  // the dynamic LDS, as line staging buffers on the cluster levels
     int stage_waves; // wavefronts whose staging buffer fits in it
+    int stage_bytes; // its size
 };
 __shared__ ClusterState g_cl;
 
@@ -705,6 +708,7 @@ struct ClusterTeam {
 __device__ inline void cluster_stage(uint8_t* lds, int lds_bytes, int64_t per_wave) {
     g_cl.stage = lds;
     g_cl.stage_waves = (int)(lds_bytes / per_wave);
+    g_cl.stage_bytes = lds_bytes;
 }
 
 // Cluster of one workgroup (the adjoint kernel, small grids).
@@ -713,7 +717,7 @@ __device__ inline void cluster_init_single() {
         g_cl.K = 1; g_cl.member = 0; g_cl.base = 0; g_cl.size = (int)blockDim.x;
         g_cl.flags = nullptr; g_cl.err = nullptr; g_cl.here = nullptr; g_cl.slots = nullptr;
         g_cl.gen = 0u; g_cl.gen_here = 0ull; g_cl.local = 1; g_cl.failed = 0; g_cl.wait = 0;
-        g_cl.stage = nullptr; g_cl.stage_waves = 0;  // no line staging unless cluster_stage says so
+        g_cl.stage = nullptr; g_cl.stage_waves = 0; g_cl.stage_bytes = 0;  // no line staging unless cluster_stage says so
     }
     __syncthreads();
 }
@@ -733,7 +737,7 @@ __device__ inline void cluster_init(int K, int member, double* sp, uint64_t wait
         if (member == 0) *g_cl.here = 0ull;  // in the L2 of a cluster on one XCD before any member passes the next barrier
         g_cl.local = 0;  // the placement check itself uses the agent-scope protocol
         g_cl.failed = 0;
-        g_cl.stage = nullptr; g_cl.stage_waves = 0;  // no line staging unless cluster_stage says so
+        g_cl.stage = nullptr; g_cl.stage_waves = 0; g_cl.stage_bytes = 0;  // no line staging unless cluster_stage says so
         sp[kClusterXcc + member] = (double)xcc_id();
     }
     cluster_barrier();
@@ -1502,26 +1506,28 @@ template <typename T> __device__ inline T wave_above(T v) { return dpp_row<0x130
 // clamped indices.  Per iteration, level 0 down: 128x64 in one workgroup 11.5
 // and 12.4 -> 10.2 and 11.6 us (pressure, transport), 256x128 on 8 workgroups
 // 11.9 and 10.1 -> 10.9 and 9.2.
-template <typename T, class Team, int ASF, int ASC, bool kSplit>
-__device__ inline void restrict_pairs(const LV<T, ASF>& F, const LV<T, ASC>& C) {
+// Coarse rows J0 .. J1 - 1 by `size` threads.
+template <typename T, int ASF, int ASC, bool kSplit>
+__device__ inline void restrict_pairs(typename AsPtr<T, ASF>::type r, int nx, int ny, const LV<T, ASC>& C, int J0, int J1,
+                                      int rank, int size) {
     using V2 = T __attribute__((ext_vector_type(2)));
-    const int hc = C.nx >> 1, n = hc * C.ny, sh = log2i(hc);
-    for (int k = Team::rank(); k < n; k += Team::size()) {  // whole wavefronts: n and the team's size are multiples of 64
-        const int J = k >> sh, m = k & (hc - 1);
+    const int hc = C.nx >> 1, n = hc * (J1 - J0), sh = log2i(hc);
+    for (int k = rank; k < n; k += size) {  // whole rows
+        const int J = J0 + (k >> sh), m = k & (hc - 1);
         T s[2] = {};
 #pragma unroll
         for (int bq = 0; bq < 4; ++bq) {
             if (!kSplit && !(bq & 1)) continue;  // odd fine rows: zero
             const int jf = 2 * J - 1 + bq;
-            const bool jin = jf >= 0 && jf < F.ny;
-            const int jc = min(max(jf, 0), F.ny - 1);
+            const bool jin = jf >= 0 && jf < ny;
+            const int jc = min(max(jf, 0), ny - 1);
             T f[6] = {};  // fine columns 4m - 1 .. 4m + 4
             if constexpr (kSplit) {
-                const V2 a = *(typename AsPtr<V2, ASF>::type)(F.r + jc * F.nx + 2 * m);
+                const V2 a = *(typename AsPtr<V2, ASF>::type)(r + jc * nx + 2 * m);
                 if (bq & 1) { f[1] = a[0]; f[3] = a[1]; f[5] = wave_above((T)a[0]); }
                 else { f[0] = wave_below((T)a[1]); f[2] = a[0]; f[4] = a[1]; }
             } else {
-                const Vec4<T> a = *(typename AsPtr<Vec4<T>, ASF>::type)(F.r + jc * F.nx + 4 * m);
+                const Vec4<T> a = *(typename AsPtr<Vec4<T>, ASF>::type)(r + jc * nx + 4 * m);
                 f[0] = wave_below((T)a[3]); f[5] = wave_above((T)a[0]);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) f[1 + q] = a[q];
@@ -1534,7 +1540,7 @@ __device__ inline void restrict_pairs(const LV<T, ASF>& F, const LV<T, ASC>& C) 
                 for (int aq = 0; aq < 4; ++aq) {
                     if (kSplit && ((aq + bq) & 1)) continue;  // black cells: zero
                     const int ifn = 2 * I - 1 + aq;
-                    row += ifn >= 0 && ifn < F.nx ? rounded_mul((T)rweight(I, C.nx, aq), f[2 * u + aq]) : (T)0;
+                    row += ifn >= 0 && ifn < nx ? rounded_mul((T)rweight(I, C.nx, aq), f[2 * u + aq]) : (T)0;
                 }
                 s[u] += jin ? rounded_mul((T)rweight(J, C.ny, bq), row) : (T)0;
             }
@@ -1556,7 +1562,8 @@ template <typename T, class Team = BlockTeam, int ASF = 0, int ASC = 0, bool kSp
 __device__ void restrict_residual(const Level<T>& F0, Level<T>& C0) {
     const LV<T, ASF> F(F0);
     const LV<T, ASC> C(C0);
-    if (F.nx >= 64 && F.nx <= 256) return restrict_pairs<T, Team, ASF, ASC, kSplit>(F, C);
+    if (F.nx >= 64 && F.nx <= 256)
+        return restrict_pairs<T, ASF, ASC, kSplit>(F.r, F.nx, F.ny, C, 0, C.ny, Team::rank(), Team::size());
     if (kTBatch > 1 && ASF == 1 && C.nx * C.ny > Team::size())
         restrict_residual_kb<T, Team, ASF, ASC, kSplit, kTBatch>(F, C);
     else restrict_residual_kb<T, Team, ASF, ASC, kSplit, 1>(F, C);
@@ -2342,19 +2349,24 @@ __device__ inline void store_c(typename AsPtr<T, AS>::type p, const T (&x)[C]) {
     }
 }
 
-template <typename T, class Team, int AS, int C>
+// The thread's cells are those of positions kr .. kr + C - 1 of row j, if
+// active; x is the level's (XS = AS), or that of rows lo .. hi - 1 in LDS.
+template <typename T, class Team, int AS, int XS, int C>
 struct RbOwn {
+    using XP = typename AsPtr<T, XS>::type;
     const LV<T, AS>& v;
-    int nx, ny, half, j, kr, o;  // o: column 2 (kr + q) + o of the red cells, 1 - o of the black ones
+    XP lds;
+    int lo, hi;
+    int nx, half, j, kr, o;  // o: column 2 (kr + q) + o of the red cells, 1 - o of the black ones
     bool active;
     T cw[2][C], ce[2][C], cs[2][C], cn[2][C], cd[2][C], dred[C], b[2][C], x[2][C];
 
-    __device__ inline RbOwn(const LV<T, AS>& lv) : v(lv) {
-        nx = v.nx; ny = v.ny; half = nx >> 1;
-        const int k = Team::rank() * C, m = half * ny;
-        active = k < m;
+    // cells k .. k + C - 1 of each colour, counted from row lo
+    __device__ inline RbOwn(const LV<T, AS>& lv, XP lds, int lo, int hi, int k) : v(lv), lds(lds), lo(lo), hi(hi) {
+        nx = v.nx; half = nx >> 1;
+        active = k < half * (hi - lo);
         const int kk = active ? k : 0;
-        j = kk >> log2i(half);
+        j = lo + (kk >> log2i(half));
         kr = kk & (half - 1);
         o = j & 1;
         const bool hs = j > 0;
@@ -2386,21 +2398,25 @@ struct RbOwn {
             }
         }
     }
+    __device__ inline XP x_row(int jr) const {
+        if constexpr (XS == AS) return v.x + jr * nx;
+        else return lds + (jr - lo) * nx;
+    }
     __device__ inline void put(int c) const {
-        if (active) store_c<C, T, AS>(v.x + j * nx + c * half + kr, x[c]);
+        if (active) store_c<C, T, XS>(x_row(j) + c * half + kr, x[c]);
     }
     // the neighbours of the cells of colour c: win[q], win[q + 1] west and east
     __device__ inline void neighbours(int c, T (&win)[C + 1], T (&xs)[C], T (&xn)[C]) const {
         const int oc = o ^ c;
-        load_c<C, T, AS>(v.x + (j > 0 ? j - 1 : j) * nx + (1 - c) * half + kr, xs);
-        load_c<C, T, AS>(v.x + (j + 1 < ny ? j + 1 : j) * nx + (1 - c) * half + kr, xn);
+        load_c<C, T, XS>(x_row(j > (XS == AS ? 0 : lo) ? j - 1 : j) + (1 - c) * half + kr, xs);
+        load_c<C, T, XS>(x_row(j + 1 < (XS == AS ? v.ny : hi) ? j + 1 : j) + (1 - c) * half + kr, xn);
         const T below = wave_below(x[1 - c][C - 1]), above = wave_above(x[1 - c][0]);
         win[0] = oc ? x[1 - c][0] : below;
 #pragma unroll
         for (int q = 1; q < C; ++q) win[q] = oc ? x[1 - c][q] : x[1 - c][q - 1];
         win[C] = oc ? above : x[1 - c][C - 1];
     }
-    __device__ inline void half_sweep(int c) {
+    __device__ inline void update(int c) {
         T win[C + 1], xs[C], xn[C];
         neighbours(c, win, xs, xn);
 #pragma unroll
@@ -2412,16 +2428,100 @@ struct RbOwn {
             a += cn[c][q] * xn[q];
             x[c][q] = diag_div(a, cd[c][q]);
         }
+    }
+    __device__ inline void half_sweep(int c) {
+        update(c);
         put(c);
         Team::sync();
     }
+    // the black cells of v.x with the correction prolonged from level c
+    template <int ASC>
+    __device__ inline void prolong_black(const LV<T, ASC>& c) {
+        const int hc = half >> 1;
+        // coarse cells kr - 1 .. kr + C of the rows J and Jn
+        const int J = j >> 1, Jn = (j & 1) ? min(J + 1, c.ny - 1) : max(J - 1, 0);
+        T cj[C + 2], cn[C + 2];
+#pragma unroll
+        for (int q = 0; q < C + 2; ++q) {
+            const int I = min(max(kr - 1 + q, 0), half - 1);
+            cj[q] = c.x[J * half + ((I + J) & 1) * hc + (I >> 1)];
+            cn[q] = c.x[Jn * half + ((I + Jn) & 1) * hc + (I >> 1)];
+        }
+        load_c<C, T, AS>(v.x + j * nx + half + kr, x[1]);
+#pragma unroll
+        for (int q = 0; q < C; ++q)
+            x[1][q] = x[1][q] + (o ? prolonged(cj[q + 1], cj[q], cn[q + 1], cn[q])
+                                   : prolonged(cj[q + 1], cj[q + 2], cn[q + 1], cn[q + 2]));
+    }
 };
 
-// Pre-smoothing (two sweeps from x = 0) and the red cells' residual.
-template <typename T, class Team, int AS, int C>
-__device__ __attribute__((noinline)) void rb_down(const Level<T>& v0) {
+// Prolongation from level c and the post-smoothing (two sweeps).  A half-sweep
+// replaces the cells of its colour, so only the black cells, as the first
+// red half-sweep's neighbours, are ever read with the correction.  (Each
+// thread adding it to the black cells it loads, without the pass that stores
+// them, was no faster: 64x32 3.3 -> 3.7 us a leg, 128x64 in one workgroup
+// 5.2 -> 7.9.)
+template <typename T, class Team, int ASC, int AS, int C>
+__device__ __attribute__((noinline)) void rb_up(const Level<T>& c0, const Level<T>& v0) {
+    const LV<T, ASC> c(c0);
     const LV<T, AS> v(v0);
-    RbOwn<T, Team, AS, C> R(v);
+    RbOwn<T, Team, AS, AS, C> R(v, v.x, 0, v.ny, Team::rank() * C);
+    R.prolong_black(c);
+    R.put(1);
+    Team::sync();
+    for (int s = 0; s < 2; ++s) {
+        R.half_sweep(0);
+        R.half_sweep(1);
+    }
+}
+
+// ------------------------------------------------------------------ strips of a level
+// A pressure level of a cluster, by strips of ny / K rows: each member smooths
+// its strip with a halo of rows beside it, x in its LDS, so that the
+// half-sweeps of a leg meet at the workgroup's barrier and only its end at the
+// cluster's (a half-sweep took 1.8 us with the cluster's barrier and loads
+// from L2, against 0.6 in a workgroup).  A halo cell is formed from the same
+// values by the same operations as its owner forms it, as far as it is used:
+// a half-sweep of n that are still to come needs n rows beside the strip.
+// The LDS is that of the levels the leader runs (g_cl.stage), idle meanwhile.
+// Per iteration, legs down and up: 256x128 on 8 workgroups 10.9 and 9.3 -> 5.4
+// and 6.3 us, its level 1 7.4 and 7.6 -> 3.4 and 3.7, 128x64 on 4 9.7 and 9.2
+// -> 3.9 and 5.2, on 2 9.6 and 9.3 -> 5.3 and 6.8.
+constexpr int kStripDown = 5, kStripUp = 4;  // halo rows
+
+struct Strip { int j0, j1, lo, hi; };  // own rows, rows held
+__device__ inline Strip strip_of(int ny, int halo) {
+    const int rows = ny / g_cl.K, j0 = g_cl.member * rows;
+    return {j0, j0 + rows, max(j0 - halo, 0), min(j0 + rows + halo, ny)};
+}
+
+// Cells of one colour per thread (0: the level is not taken by strips): four,
+// or eight where a strip and its halo need them (128x64 on 2 workgroups and
+// 256x128 on 8).  Levels of 512 columns and more do not fit in one pass.
+template <typename T, class Team, int AS>
+__device__ inline int strip_cells(int nx, int ny) {
+    if constexpr (!std::is_same<Team, ClusterTeam>::value || AS != 1) return 0;
+    const int K = g_cl.K;
+    if (K == 1 || nx < 64 || nx > 256 || ny < 2 * K) return 0;
+    const int rows = ny / K + 2 * kStripDown;
+    if (rows * nx * (int)sizeof(T) > g_cl.stage_bytes) return 0;
+    const int m = rows * (nx >> 1), ts = (int)blockDim.x;
+    return m <= 4 * ts ? 4 : kStripWide && sizeof(T) == 4 && m <= 8 * ts ? 8 : 0;
+}
+
+// Pre-smoothing (two sweeps from x = 0) and the red cells' residual; a strip
+// (XS = 3 of a level in global memory) restricts it too.
+template <typename T, class Team, int AS, int XS, int C>
+__device__ __attribute__((noinline)) void rb_down(const Level<T>& c0, const Level<T>& v0) {
+    constexpr bool kStrip = XS != AS;
+    const LV<T, AS> v(v0);
+    Strip s = {0, 0, 0, v.ny};
+    typename AsPtr<T, XS>::type lds = {};
+    if constexpr (kStrip) {
+        s = strip_of(v.ny, kStripDown);
+        lds = as_ptr<3>(reinterpret_cast<T*>(g_cl.stage));
+    }
+    RbOwn<T, Team, AS, XS, C> R(v, lds, s.lo, s.hi, Team::rank() * C);
 #pragma unroll
     for (int q = 0; q < C; ++q) R.x[0][q] = diag_div(R.b[0][q], R.cd[0][q]);
     R.put(0);
@@ -2439,42 +2539,48 @@ __device__ __attribute__((noinline)) void rb_down(const Level<T>& v0) {
         ax -= R.cn[0][q] * xn[q];
         r[q] = R.b[0][q] - ax;
     }
-    if (R.active) store_c<C, T, AS>(v.r + R.j * R.nx + R.kr, r);
-    Team::sync();
+    if constexpr (!kStrip) {
+        if (R.active) store_c<C, T, AS>(v.r + R.j * R.nx + R.kr, r);
+        Team::sync();
+    } else {
+        if (R.active) {
+            store_c<C, T, XS>(R.x_row(R.j) + R.kr, r);  // the red cells' x is not read again
+            if (R.j >= s.j0 && R.j < s.j1) {
+                store_c<C, T, AS>(v.x + R.j * R.nx + R.kr, R.x[0]);
+                store_c<C, T, AS>(v.x + R.j * R.nx + R.half + R.kr, R.x[1]);
+            }
+        }
+        Team::sync();
+        restrict_pairs<T, XS, AS, true>(lds - s.lo * v.nx, v.nx, v.ny, LV<T, AS>(c0), s.j0 >> 1, s.j1 >> 1, Team::rank(),
+                                        Team::size());
+    }
 }
 
-// Prolongation from level c and the post-smoothing (two sweeps).  A half-sweep
-// replaces the cells of its colour, so only the black cells, as the first
-// red half-sweep's neighbours, are ever read with the correction.  (Each
-// thread adding it to the black cells it loads, without the pass that stores
-// them, was no faster: 64x32 3.3 -> 3.7 us a leg, 128x64 in one workgroup
-// 5.2 -> 7.9.)
-template <typename T, class Team, int ASC, int AS, int C>
-__device__ __attribute__((noinline)) void rb_up(const Level<T>& c0, const Level<T>& v0) {
-    const LV<T, ASC> c(c0);
-    const LV<T, AS> v(v0);
-    RbOwn<T, Team, AS, C> R(v);
-    const int j = R.j, kr = R.kr, half = R.half, hc = half >> 1;
-    // coarse cells kr - 1 .. kr + C of the rows J and Jn
-    const int J = j >> 1, Jn = (j & 1) ? min(J + 1, c.ny - 1) : max(J - 1, 0);
-    T cj[C + 2], cn[C + 2];
-#pragma unroll
-    for (int q = 0; q < C + 2; ++q) {
-        const int I = min(max(kr - 1 + q, 0), half - 1);
-        cj[q] = c.x[J * half + ((I + J) & 1) * hc + (I >> 1)];
-        cn[q] = c.x[Jn * half + ((I + Jn) & 1) * hc + (I >> 1)];
-    }
-    load_c<C, T, AS>(v.x + j * R.nx + half + kr, R.x[1]);
-#pragma unroll
-    for (int q = 0; q < C; ++q)
-        R.x[1][q] = R.x[1][q] + (R.o ? prolonged(cj[q + 1], cj[q], cn[q + 1], cn[q])
-                                     : prolonged(cj[q + 1], cj[q + 2], cn[q + 1], cn[q + 2]));
+// Other members read the level's x in their halo meanwhile: the result goes
+// to r's array, and the two change places.
+template <typename T, int C>
+__device__ __attribute__((noinline)) void strip_up(const Level<T>& c0, Level<T>& v0) {
+    const LV<T, 1> v(v0), c(c0);
+    const Strip s = strip_of(v.ny, kStripUp);
+    const auto x = as_ptr<3>(reinterpret_cast<T*>(g_cl.stage));
+    RbOwn<T, BlockTeam, 1, 3, C> R(v, x, s.lo, s.hi, (int)threadIdx.x * C);
+    R.prolong_black(c);
     R.put(1);
-    Team::sync();
-    for (int s = 0; s < 2; ++s) {
-        R.half_sweep(0);
-        R.half_sweep(1);
+    __syncthreads();
+    R.half_sweep(0);
+    R.half_sweep(1);
+    R.half_sweep(0);
+    R.update(1);
+    if (R.active && R.j >= s.j0 && R.j < s.j1) {
+        store_c<C, T, 1>(v.r + R.j * R.nx + R.kr, R.x[0]);
+        store_c<C, T, 1>(v.r + R.j * R.nx + R.half + R.kr, R.x[1]);
     }
+    if (threadIdx.x == 0) {
+        T* const t = v0.x;
+        v0.x = v0.r;
+        v0.r = t;
+    }
+    ClusterTeam::sync();
 }
 
 // Cells of one colour per thread when the level takes one such pass of the
@@ -2504,10 +2610,14 @@ __device__ void vdown(Solve<T>& S, int l) {
             Team::sync();
         }
     } else {
+        switch (strip_cells<T, Team, AS>(v.nx, v.ny)) {
+            case 4: rb_down<T, BlockTeam, 1, 3, 4>(c, v); Team::sync(); return;
+            case 8: if constexpr (kStripWide && sizeof(T) == 4) { rb_down<T, BlockTeam, 1, 3, 8>(c, v); Team::sync(); return; }
+        }
         switch (rb_cells<Team>(v.nx, v.ny)) {
-            case 1: rb_down<T, Team, AS, 1>(v); break;
-            case 2: rb_down<T, Team, AS, 2>(v); break;
-            case 4: rb_down<T, Team, AS, 4>(v); break;
+            case 1: rb_down<T, Team, AS, AS, 1>(c, v); break;
+            case 2: rb_down<T, Team, AS, AS, 2>(c, v); break;
+            case 4: rb_down<T, Team, AS, AS, 4>(c, v); break;
             default:
                 rbgs<T, Team, AS>(v, 2);
                 level_residual<T, kTransport, kTrans, Team, AS>(v);
@@ -2535,6 +2645,10 @@ __device__ void vup(Solve<T>& S, int l) {
             case 256: return line_up<T, kTrans, 64, Team, ASN, AS>(c, v);
         }
     } else {
+        switch (strip_cells<T, Team, AS>(v.nx, v.ny)) {
+            case 4: return strip_up<T, 4>(c, v);
+            case 8: if constexpr (kStripWide && sizeof(T) == 4) return strip_up<T, 8>(c, v);
+        }
         switch (rb_cells<Team>(v.nx, v.ny)) {
             case 1: return rb_up<T, Team, ASN, AS, 1>(c, v);
             case 2: return rb_up<T, Team, ASN, AS, 2>(c, v);

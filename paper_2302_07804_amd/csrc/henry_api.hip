@@ -229,11 +229,12 @@ int check_opts(const henry_opts_t* o) {
 //  - the batch's costliest grid of that size (`lead`): one workgroup per 2048
 //    fine cells, as long as its workgroups leave half the 256 CUs to the
 //    batch's other groups, or take all of them when there are none.  ms of
-//    8 to 40 steps with 1, 2, 4, 8 per solve: 16 solves of 128x64 54, 48, 43,
-//    44; 64 of them 60, 59, 56, -; 16 of 256x128 212, 165, 116, 91; 64 of
-//    them 244, 195, 142, -.  L = 4 batch with 4 and 8 per 256x128 solve: 342
-//    and 264; a L = 3 batch with 1, 2, 4 per 128x64 solve (64 of them): 120,
-//    101, 113.
+//    200 steps with 1, 2, 4, 8 per solve: 16 solves of 128x64 66, 52, 45,
+//    45; 64 of them 74, 59, 53, 100; 128 of them 76, 64, 106, -; 160 of them
+//    81, 114, -, -; 16 of 256x128 295, 207, 142, 100; 64 of them 353, 253,
+//    182, 214.  With other groups beside (when the line was drawn): L = 4
+//    batch with 4 and 8 per 256x128 solve 342 and 264; a L = 3 batch with 1,
+//    2, 4 per 128x64 solve (64 of them) 120, 101, 113.
 //  - other grids, which would run after it on the cluster stream: one per
 //    8192 (L = 4 batch with 2 per 128x64 solve too: 385 ms).
 int cluster_size(int nx, int ny, int nsolves, int requested, bool lead, bool alone) {

@@ -612,6 +612,11 @@ __device__ inline unsigned long long l2_fetch_add(unsigned long long* p, unsigne
     return old;
 }
 
+// The same without the value before.
+__device__ inline void l2_add(unsigned long long* p, unsigned long long v) {
+    asm volatile("global_atomic_add_x2 %0, %1, off\n\ts_waitcnt vmcnt(0)" : : "v"(p), "v"(v) : "memory");
+}
+
 constexpr int kFailBit = 56;
 
 // The bound of a wait: the wall clock is first read after a poll that found
@@ -657,7 +662,7 @@ __device__ inline void cluster_barrier() {
                     v = l2_fetch_add(here, 0ull);
                 }
                 if (failed) {
-                    l2_fetch_add(here, 1ull << kFailBit);
+                    l2_add(here, 1ull << kFailBit);
                     __hip_atomic_store(g_cl.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     g_cl.failed = 1;
                 }

@@ -391,7 +391,11 @@ int henry_level_smooth(henry_ctx* ctx, int32_t nx, int32_t ny, int32_t kind, int
  *            per solve; -1 = built-in plan.  Groups with clusters always
  *            run on stream 0, one after another.
  * threads = cluster = 0 and stream = -1 clear the entry.  None of the
- * choices changes a result (bitwise).  The measuring driver that fills it
+ * choices changes a result (bitwise), but for dq_dxi and dq_dq of
+ * henry_adjoint_batch: their sums over cells are taken by thread, in the
+ * order of the tuned workgroup size (of the built-in one without a tuned or
+ * requested size, which does not depend on the number of solves here).
+ * The measuring driver that fills it
  * times candidates on short runs of the caller's own batch (Python
  * binding: paper_2302_07804_amd.autotune).  henry_tune_get returns the
  * workgroup size of a group of one workgroup per solve (of up to 512

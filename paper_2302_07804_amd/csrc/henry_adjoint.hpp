@@ -36,6 +36,7 @@ struct AdjLaunch {
     double* dq_dlogk;   // packed per cell or null
     double* dq_dphi;    // packed per cell or null
     double* dq_dq;      // [nsolves] or null
+    int32_t sum_threads;  // workgroup size whose order the sums over cells take (block_sums)
 };
 
 __host__ __device__ inline int num_ckpts(int nsteps, int k) { return (nsteps + k - 1) / k; }
@@ -58,10 +59,11 @@ __host__ __device__ inline int64_t adjoint_bytes(int nx, int ny, int nsteps, int
 
 struct Adj {
     double *mu_p, *mu_c, *lam_p, *lam_c, *dinv_p, *dinv_c, *b_p, *b_c, *gK, *gphi, *mh, *scr, *ckpt, *seg;
-    int k, ncp;
+    int k, ncp, nt;  // nt: AdjLaunch::sum_threads
 };
 
-__device__ inline void bind_adj(Adj& A, uint8_t* base, int n, int nsteps, int k) {
+__device__ inline void bind_adj(Adj& A, uint8_t* base, int n, int nsteps, int k, int nt) {
+    A.nt = nt;
     double* f = reinterpret_cast<double*>(base);
     A.mu_p = f; A.mu_c = f + n; A.lam_p = f + 2 * n; A.lam_c = f + 3 * n; A.dinv_p = f + 4 * n;
     A.dinv_c = f + 5 * n;
@@ -71,6 +73,28 @@ __device__ inline void bind_adj(Adj& A, uint8_t* base, int n, int nsteps, int k)
     A.ncp = num_ckpts(nsteps, k);
     A.ckpt = f + 16 * n + 8;
     A.seg = A.ckpt + (int64_t)A.ncp * ckpt_doubles(n);
+}
+
+// Two sums over cells at once, in the order in which a workgroup of nt
+// threads takes them (each thread its own cells in turn, then block_sum),
+// whatever the size of this one: add(t, a, b) adds the cells of thread t of
+// nt.  The built-in workgroup is half as large for a batch of many solves, and
+// a sample's gradient must not depend on how many others are solved with it.
+// nt and blockDim are multiples of 64 and nt <= 1024 (red holds 32 doubles).
+template <class F>
+__device__ inline void block_sums(int nt, double* red, double& ra, double& rb, F&& add) {
+    __syncthreads();
+    for (int t = threadIdx.x; t < nt; t += blockDim.x) {
+        double a = 0.0, b = 0.0;
+        add(t, a, b);
+        a = wave_sum(a);
+        b = wave_sum(b);
+        if ((t & (kWave - 1)) == 0) { red[2 * (t / kWave)] = a; red[2 * (t / kWave) + 1] = b; }
+    }
+    __syncthreads();
+    ra = red[0];
+    rb = red[1];
+    for (int w = 1; w < nt / kWave; ++w) { ra += red[2 * w]; rb += red[2 * w + 1]; }
 }
 
 // ------------------------------------------------------------------ flux derivatives (FP64)
@@ -282,16 +306,17 @@ __device__ double jt_pass(const Phys& ph, Solve<T>& S, Adj& A, double* red, int 
         return r;
     }
     // lam^T dR/dq: the recharge faces of the first column, summed by the
-    // leader in the order of a one-workgroup pass (thread t adds the cells
-    // t, t + blockDim, ... in turn), so the sum is the same for every
+    // leader in the order of a one-workgroup pass (thread t of A.nt adds the
+    // cells t, t + A.nt, ... in turn), so the sum is the same for every
     // cluster size
     if (g_cl.member == 0) {
-        double gq = 0.0;
-        for (int j = 0; j < ny; ++j) {
-            const int idx = j * nx;
-            if ((idx & ((int)blockDim.x - 1)) == (int)threadIdx.x) gq += lp[idx] * (-ph.rho0 * h);
-        }
-        const double g = block_sum(gq, red);
+        double g, unused;
+        block_sums(A.nt, red, g, unused, [&](int t, double& gq, double&) {
+            for (int j = 0; j < ny; ++j) {
+                const int idx = j * nx;
+                if ((idx & (A.nt - 1)) == t) gq = fused(lp[idx], -ph.rho0 * h, gq);
+            }
+        });
         if (threadIdx.x == 0) A.scr[0] -= g;
     }
     ClusterTeam::sync();
@@ -469,7 +494,7 @@ __global__ void __launch_bounds__(512) henry_adjoint_kernel(Launch lp, AdjLaunch
         S.tau = ph.T / d.nsteps;
         S.ph = ph;
         S.q = S.scratch[0];
-        bind_adj(A, lp.ws + d.adj_off, d.nx * d.ny, d.nsteps, al.ckpt);
+        bind_adj(A, lp.ws + d.adj_off, d.nx * d.ny, d.nsteps, al.ckpt, al.sum_threads);
     }
     __syncthreads();
     if (lp.cluster > 1) cluster_init(lp.cluster, member, S.scratch, lp.cluster_wait);
@@ -543,48 +568,48 @@ __global__ void __launch_bounds__(512) henry_adjoint_kernel(Launch lp, AdjLaunch
     if (member != 0) return;
     const double gq = A.scr[0];
     const double h = S.h;
-    double g1 = 0.0, g2 = 0.0;
     const double x1 = lp.field_kind == 3 ? lp.xi[3 * d.index] : 0.0;
     const double x2 = lp.field_kind == 3 ? lp.xi[3 * d.index + 1] : 0.0;
     const double kappa = ph.k0 * (1.0 - ph.phi0 * ph.phi0) / (ph.phi0 * ph.phi0 * ph.phi0);
-    for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
-        const double KP = S.K[idx];
-        if (al.dq_dlogk) al.dq_dlogk[d.field_off + idx] = A.gK[idx] * KP;
-        if (al.dq_dphi) al.dq_dphi[d.field_off + idx] = A.gphi[idx];
-        if (lp.field_kind == 0) {
-            const int i = idx % S.nx, j = idx / S.nx;
-            const double x = (i + 0.5) * h, y = -1.0 + (j + 0.5) * h;
-            // derivatives of the closed-form fields with respect to xi1, xi2
-            g1 += A.gphi[idx] * ph.phi0 * 0.2 * cos(M_PI * x / 2.0) * cos(M_PI * y);
-            g2 += A.gK[idx] * KP * 0.5 * sin(M_PI * x / 2.0);
-        } else if (lp.field_kind == 3) {
-            // two-layer porosity: phi = phi0 B C0 with B = 1 + 0.15 (xi2 a + xi1 b),
-            // C0 = 1 +- 0.2 xi1; K = kappa phi^3 / (1 - phi^2), so
-            // dK/dphi = kappa phi^2 (3 - phi^2) / (1 - phi^2)^2
-            const int i = idx % S.nx, j = idx / S.nx;
-            const double x = (i + 0.5) * h, y = -1.0 + (j + 0.5) * h;
-            const double a = cos(M_PI * x / 2.0) + sin(2.0 * M_PI * y), b = cos(2.0 * M_PI * x);
-            const double sg = y < -0.75 ? 0.2 : -0.2;
-            const double B = 1.0 + 0.15 * (x2 * a + x1 * b), C0 = 1.0 + sg * x1;
-            const double fP = S.phi[idx], f2 = fP * fP;
-            const double gphi = A.gphi[idx] + A.gK[idx] * kappa * f2 * (3.0 - f2) / ((1.0 - f2) * (1.0 - f2));
-            g1 += gphi * ph.phi0 * (0.15 * b * C0 + B * sg);
-            g2 += gphi * ph.phi0 * 0.15 * a * C0;
+    double g1, g2;
+    block_sums(A.nt, red, g1, g2, [&](int t, double& g1, double& g2) {
+        for (int idx = t; idx < n; idx += A.nt) {
+            const double KP = S.K[idx];
+            if (al.dq_dlogk) al.dq_dlogk[d.field_off + idx] = A.gK[idx] * KP;
+            if (al.dq_dphi) al.dq_dphi[d.field_off + idx] = A.gphi[idx];
+            if (lp.field_kind == 0) {
+                const int i = idx % S.nx, j = idx / S.nx;
+                const double x = (i + 0.5) * h, y = -1.0 + (j + 0.5) * h;
+                // derivatives of the closed-form fields with respect to xi1, xi2
+                g1 = fused(A.gphi[idx] * ph.phi0 * 0.2 * cos(M_PI * x / 2.0), cos(M_PI * y), g1);
+                g2 = fused(A.gK[idx] * KP * 0.5, sin(M_PI * x / 2.0), g2);
+            } else if (lp.field_kind == 3) {
+                // two-layer porosity: phi = phi0 B C0 with B = 1 + 0.15 (xi2 a + xi1 b),
+                // C0 = 1 +- 0.2 xi1; K = kappa phi^3 / (1 - phi^2), so
+                // dK/dphi = kappa phi^2 (3 - phi^2) / (1 - phi^2)^2
+                const int i = idx % S.nx, j = idx / S.nx;
+                const double x = (i + 0.5) * h, y = -1.0 + (j + 0.5) * h;
+                const double a = cos(M_PI * x / 2.0) + sin(2.0 * M_PI * y), b = cos(2.0 * M_PI * x);
+                const double sg = y < -0.75 ? 0.2 : -0.2;
+                const double B = 1.0 + 0.15 * (x2 * a + x1 * b), C0 = 1.0 + sg * x1;
+                const double fP = S.phi[idx], f2 = fP * fP;
+                const double gphi = A.gphi[idx] + A.gK[idx] * kappa * f2 * (3.0 - f2) / ((1.0 - f2) * (1.0 - f2));
+                g1 = fused(gphi * ph.phi0, 0.15 * b * C0 + B * sg, g1);
+                g2 = fused(gphi * ph.phi0 * 0.15 * a, C0, g2);
+            }
         }
-    }
-    g1 = block_sum(g1, red);
-    g2 = block_sum(g2, red);
+    });
     if (lp.field_kind == 2 && al.dq_dxi) {
         // KL coefficients: dphi/dxi_k = phi0 s_phi m_k, dK/dxi_{20+k} = K s_K m_k
         for (int k = 0; k < 20; ++k) {
-            double ap = 0.0, ak = 0.0;
-            for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
-                const double m = lp.kl_modes[(size_t)k * n + idx];
-                ap += A.gphi[idx] * m;
-                ak += A.gK[idx] * S.K[idx] * m;
-            }
-            ap = block_sum(ap, red);
-            ak = block_sum(ak, red);
+            double ap, ak;
+            block_sums(A.nt, red, ap, ak, [&](int t, double& ap, double& ak) {
+                for (int idx = t; idx < n; idx += A.nt) {
+                    const double m = lp.kl_modes[(size_t)k * n + idx];
+                    ap = fused(A.gphi[idx], m, ap);
+                    ak = fused(A.gK[idx] * S.K[idx], m, ak);
+                }
+            });
             if (threadIdx.x == 0) {
                 al.dq_dxi[41 * d.index + k] = ap * ph.phi0 * lp.kl_sigma_phi;
                 al.dq_dxi[41 * d.index + 20 + k] = ak * lp.kl_sigma_logk;

@@ -119,6 +119,7 @@ __global__ void desc_fill_kernel(DescChunk ch, henry::SolveDesc* table) {
 
 struct Group {
     int nx, ny, threads, cluster;
+    int sum_threads = 0;       // adjoint: see henry::block_sums
     int stream = -1;           // tuned stream of a one-workgroup group, -1 = built-in plan
     std::vector<int> members;  // indices into the solve list
     double cost;
@@ -1076,7 +1077,9 @@ int henry_adjoint_batch(henry_ctx* ctx, const henry_grid_t* solves, int32_t nsol
         int t = o->threads;
         if (t == 0)
             t = tu.threads > 0 ? tu.threads : group_threads(G.nx, G.ny, (int)G.members.size(), prec, kManyAdjoints);
+        const bool built_in = o->threads == 0 && tu.threads == 0;
         G.threads = std::min(t, kAdjMaxThreads);
+        G.sum_threads = std::min(built_in ? default_threads(G.nx, G.ny, prec) : t, kAdjMaxThreads);
         G.cluster = cluster_size(G.nx, G.ny, (int)G.members.size(), o->cluster > 0 ? o->cluster : tu.cluster,
                                  lead >= 0 && &G == &order[lead], order.size() == 1);
         G.stream = tu.stream;
@@ -1140,6 +1143,7 @@ int henry_adjoint_batch(henry_ctx* ctx, const henry_grid_t* solves, int32_t nsol
         l.lds_block_cells = lds_block_cells(prec);
         const size_t lds = lds_bytes(G.nx, G.ny, prec);  // no line staging in the adjoint kernel
         l.lds_bytes = (int32_t)lds;
+        al.sum_threads = G.sum_threads;
         if (prec == HENRY_PREC_MIXED)
             hipLaunchKernelGGL(henry::henry_adjoint_kernel<float>, dim3(nblk), dim3(G.threads), lds, st, l, al);
         else

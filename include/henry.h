@@ -136,7 +136,11 @@ typedef struct {
     int32_t cluster_wait_us;  /* bound of one wait at a cluster barrier, in
                                  microseconds; 0 = 10 s.  A member that waits
                                  longer stops its cluster: the solve reports
-                                 HENRY_STATUS_SYNC.                              */
+                                 HENRY_STATUS_SYNC (other work may hold the CUs
+                                 that a cluster's last members wait for).  With
+                                 the built-in number of workgroups, solves of
+                                 fewer than 16384 cells do not: one workgroup
+                                 solves them again.                              */
     int32_t predictor;        /* start of each step's iteration, extrapolated
                                  through the last converged states: 1 = the
                                  interpolating polynomial through up to four;

@@ -486,6 +486,7 @@ __global__ void __launch_bounds__(512) henry_adjoint_kernel(Launch lp, AdjLaunch
     cluster_of_block(lp.cluster, cid, member);
     if (cid >= lp.nsolves) return;
     const SolveDesc d = lp.descs[cid];
+    if (d.nsteps == 0) return;  // henry_redo_kernel
     const Phys& ph = lp.ph;
     if (threadIdx.x == 0) {
         bind_solve(S, lp.ws + d.ws_off, d.nx, d.ny, lds_levels, lp.lds_cells, lp.lds_block_cells);
@@ -497,7 +498,7 @@ __global__ void __launch_bounds__(512) henry_adjoint_kernel(Launch lp, AdjLaunch
         bind_adj(A, lp.ws + d.adj_off, d.nx * d.ny, d.nsteps, al.ckpt, al.sum_threads);
     }
     __syncthreads();
-    if (lp.cluster > 1) cluster_init(lp.cluster, member, S.scratch, lp.cluster_wait);
+    if (lp.cluster > 1) cluster_init(lp.cluster, member, S.scratch, lp.cluster_wait, lp.redo);
     else cluster_init_single();
     // no line staging here: the transposed cycles reuse the LDS levels'
     // coefficients from one cycle to the next, so nothing may overlay them
@@ -564,8 +565,12 @@ __global__ void __launch_bounds__(512) henry_adjoint_kernel(Launch lp, AdjLaunch
     // ---- outputs, by the leader alone: its sums take the cells in the
     // order of a one-workgroup solve
     ClusterTeam::sync();
-    if (g_cl.failed) status = 3;
+    if (g_cl.failed) status = kStatusSync;
     if (member != 0) return;
+    if (g_cl.failed && g_cl.redo) {  // outputs may overlap what the solve reads when it starts again (xi)
+        if (threadIdx.x == 0) lp.status[d.index] = status;
+        return;
+    }
     const double gq = A.scr[0];
     const double h = S.h;
     const double x1 = lp.field_kind == 3 ? lp.xi[3 * d.index] : 0.0;

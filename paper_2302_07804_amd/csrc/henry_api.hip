@@ -119,6 +119,7 @@ __global__ void desc_fill_kernel(DescChunk ch, henry::SolveDesc* table) {
 
 struct Group {
     int nx, ny, threads, cluster;
+    bool redo = false;         // see redo_alone
     int sum_threads = 0;       // adjoint: see henry::block_sums
     int stream = -1;           // tuned stream of a one-workgroup group, -1 = built-in plan
     std::vector<int> members;  // indices into the solve list
@@ -248,6 +249,16 @@ int cluster_size(int nx, int ny, int nsolves, int requested, bool lead, bool alo
     return k;
 }
 
+// Built-in clusters on grids of fewer than 16384 cells (128x64): a solve whose
+// cluster's wait runs out (its members kept apart by other work that holds
+// the CUs, or by a short opts->cluster_wait_us) is solved again by one
+// workgroup, in a launch behind the cluster's that the other solves leave at
+// once, so that a call that asks for no cluster on these grids does not
+// report HENRY_STATUS_SYNC.  Same bits as with any cluster.
+bool redo_alone(int nx, int ny, int cluster, int requested) {
+    return cluster > 1 && requested <= 0 && nx * ny < 2 * 8192;
+}
+
 int64_t solve_bytes(int nx, int ny, int prec) {
     return prec == HENRY_PREC_MIXED ? henry::solve_bytes<float>(nx, ny) : henry::solve_bytes<double>(nx, ny);
 }
@@ -352,6 +363,7 @@ int enqueue_groups(henry_ctx* ctx, const std::vector<Group>& order, const std::v
         l.lds_block_cells = lds_block_cells(prec);
         const size_t lds = launch_lds_bytes(G.nx, G.ny, prec, G.threads, K);
         l.lds_bytes = (int32_t)lds;
+        l.redo = G.redo;
         const int chunk = spl > 0 ? spl : rmax;
         if (profile) {
             henry_group_time_t& pt = ctx->prof[gi];
@@ -373,6 +385,20 @@ int enqueue_groups(henry_ctx* ctx, const std::vector<Group>& order, const std::v
             } else {
                 hipLaunchKernelGGL(henry::henry_solve_kernel<double>, dim3(nblk), dim3(G.threads), lds, st, l);
             }
+        }
+        if (G.redo) {
+            hipLaunchKernelGGL(henry::henry_redo_kernel, dim3((nb + 255) / 256), dim3(256), 0, st, dtable + gstart[gi], nb,
+                               lp.status);
+            l.redo = 0;
+            l.cluster = 1;
+            l.g_begin = 0;
+            l.g_end = rmax;
+            const size_t lds1 = launch_lds_bytes(G.nx, G.ny, prec, G.threads, 1);
+            l.lds_bytes = (int32_t)lds1;
+            if (prec == HENRY_PREC_MIXED)
+                hipLaunchKernelGGL(henry::henry_solve_kernel<float>, dim3(nb), dim3(G.threads), lds1, st, l);
+            else
+                hipLaunchKernelGGL(henry::henry_solve_kernel<double>, dim3(nb), dim3(G.threads), lds1, st, l);
         }
         if (hipGetLastError() != hipSuccess) return HENRY_EHIP;
         if (profile && hipEventRecord(ctx->prof_ev[2 * gi + 1], st) != hipSuccess) return HENRY_EHIP;
@@ -720,8 +746,9 @@ int solve_batch_impl(henry_ctx* ctx, const henry_grid_t* solves, int32_t nsolves
         const Tuned tu = it != ctx->tuned.end() ? it->second : Tuned{};
         const int nb = (int)G.members.size();
         int t = o->threads;
-        G.cluster = cluster_size(G.nx, G.ny, nb, o->cluster > 0 ? o->cluster : tu.cluster, lead >= 0 && &G == &order[lead],
-                                 order.size() == 1);
+        const int asked = o->cluster > 0 ? o->cluster : tu.cluster;
+        G.cluster = cluster_size(G.nx, G.ny, nb, asked, lead >= 0 && &G == &order[lead], order.size() == 1);
+        G.redo = redo_alone(G.nx, G.ny, G.cluster, asked);
         if (t == 0 && tu.threads > 0) t = tu.threads;
         if (t == 0) t = (prec == HENRY_PREC_MIXED && G.cluster > 1) ? 512 : group_threads(G.nx, G.ny, nb, prec, kManySolves);
         G.threads = t;
@@ -1080,8 +1107,10 @@ int henry_adjoint_batch(henry_ctx* ctx, const henry_grid_t* solves, int32_t nsol
         const bool built_in = o->threads == 0 && tu.threads == 0;
         G.threads = std::min(t, kAdjMaxThreads);
         G.sum_threads = std::min(built_in ? default_threads(G.nx, G.ny, prec) : t, kAdjMaxThreads);
-        G.cluster = cluster_size(G.nx, G.ny, (int)G.members.size(), o->cluster > 0 ? o->cluster : tu.cluster,
-                                 lead >= 0 && &G == &order[lead], order.size() == 1);
+        const int asked = o->cluster > 0 ? o->cluster : tu.cluster;
+        G.cluster = cluster_size(G.nx, G.ny, (int)G.members.size(), asked, lead >= 0 && &G == &order[lead],
+                                 order.size() == 1);
+        G.redo = redo_alone(G.nx, G.ny, G.cluster, asked);
         G.stream = tu.stream;
     }
     DeviceGuard dg(ctx->device);
@@ -1144,10 +1173,21 @@ int henry_adjoint_batch(henry_ctx* ctx, const henry_grid_t* solves, int32_t nsol
         const size_t lds = lds_bytes(G.nx, G.ny, prec);  // no line staging in the adjoint kernel
         l.lds_bytes = (int32_t)lds;
         al.sum_threads = G.sum_threads;
-        if (prec == HENRY_PREC_MIXED)
-            hipLaunchKernelGGL(henry::henry_adjoint_kernel<float>, dim3(nblk), dim3(G.threads), lds, st, l, al);
-        else
-            hipLaunchKernelGGL(henry::henry_adjoint_kernel<double>, dim3(nblk), dim3(G.threads), lds, st, l, al);
+        auto launch = [&](int blocks) {
+            if (prec == HENRY_PREC_MIXED)
+                hipLaunchKernelGGL(henry::henry_adjoint_kernel<float>, dim3(blocks), dim3(G.threads), lds, st, l, al);
+            else
+                hipLaunchKernelGGL(henry::henry_adjoint_kernel<double>, dim3(blocks), dim3(G.threads), lds, st, l, al);
+        };
+        l.redo = G.redo;
+        launch(nblk);
+        if (G.redo) {
+            hipLaunchKernelGGL(henry::henry_redo_kernel, dim3((nb + 255) / 256), dim3(256), 0, st, dtable + gstart[gi], nb,
+                               lp.status);
+            l.redo = 0;
+            l.cluster = 1;
+            launch(nb);
+        }
         if (hipGetLastError() != hipSuccess) return HENRY_EHIP;
     }
     for (int k = 0; k < nstreams; ++k) {

@@ -123,6 +123,7 @@ struct Launch {
     int32_t nsolves;         // solves of this launch (descs[0 .. nsolves-1])
     int32_t cluster;         // workgroups per solve (1, 2, 4 or 8)
     uint64_t cluster_wait;   // bound of one cluster-barrier wait, ticks of the 100 MHz wall clock
+    int32_t redo;            // a solve whose cluster's wait runs out is left to another launch (henry_redo_kernel)
     // time series (forward solves only; trace == nullptr: none): record k =
     // 1..trace_nrec after step ceil(k nsteps / trace_nrec), holding the
     // fresh-water area and c at trace_npts points, at
@@ -134,6 +135,7 @@ struct Launch {
 };
 
 constexpr int kMaxTracePoints = 16;
+constexpr int kStatusSync = 3;  // HENRY_STATUS_SYNC
 
 // ------------------------------------------------------------------ layout
 __host__ __device__ inline int64_t align256(int64_t b) { return (b + 255) & ~int64_t(255); }
@@ -589,6 +591,7 @@ struct ClusterState {
     unsigned long long gen_here;  // of them through `here`, this launch
     int local;       // all members on one XCD
     int failed;
+    int redo;        // Launch::redo
     uint64_t wait;   // bound of one wait (wall-clock ticks)
     uint8_t* stage;  // the dynamic LDS, as line staging buffers on the cluster levels
     int stage_waves; // wavefronts whose staging buffer fits in it
@@ -729,9 +732,10 @@ __device__ inline void cluster_init_single() {
 
 // Binds member `member` of a K-cluster to the cluster state in the solve's
 // scratch `sp` and checks the members' placement.
-__device__ inline void cluster_init(int K, int member, double* sp, uint64_t wait) {
+__device__ inline void cluster_init(int K, int member, double* sp, uint64_t wait, int redo) {
     if (threadIdx.x == 0) {
         g_cl.wait = wait;
+        g_cl.redo = redo;
         g_cl.K = K; g_cl.member = member; g_cl.base = member * (int)blockDim.x; g_cl.size = K * (int)blockDim.x;
         g_cl.flags = reinterpret_cast<unsigned*>(sp + kClusterFlags);
         g_cl.err = reinterpret_cast<unsigned*>(sp + kClusterErr);
@@ -3010,7 +3014,7 @@ __global__ void __launch_bounds__(sizeof(T) == 4 ? HENRY_FP32_THREADS : 512) hen
     }
     __syncthreads();
     double* sp = S.scratch;
-    if (lp.cluster > 1) cluster_init(lp.cluster, member, sp, lp.cluster_wait);
+    if (lp.cluster > 1) cluster_init(lp.cluster, member, sp, lp.cluster_wait, lp.redo);
     else cluster_init_single();
     if (threadIdx.x == 0) cluster_stage(lds_levels, lp.lds_bytes, line_stage_bytes_per_wave<T>());
     const int n = S.n;
@@ -3057,9 +3061,11 @@ __global__ void __launch_bounds__(sizeof(T) == 4 ? HENRY_FP32_THREADS : 512) hen
         }
     }
     ClusterTeam::sync();
-    if (g_cl.failed) status = 3;
+    if (g_cl.failed) status = kStatusSync;
     if (member != 0) return;
-    if (nrec && (status == 2 || status == 3)) {
+    // outputs may overlap what the solve reads when it starts again (c0)
+    const bool left = g_cl.failed && g_cl.redo;
+    if (nrec && !left && (status == 2 || status == kStatusSync)) {
         // NaN in the records of step s (the step the solve stopped in, or
         // the first step of this launch) and later: the first such record is
         // k0 = floor((s - 1) nrec / N) + 1
@@ -3079,7 +3085,9 @@ __global__ void __launch_bounds__(sizeof(T) == 4 ? HENRY_FP32_THREADS : 512) hen
         for (int k = 0; k < 24; ++k) sp[8 + k] = (double)pc.acc[k];
 #endif
     }
-    if (s_end == d.nsteps) {
+    if (left) {
+        if (threadIdx.x == 0 && s_end == d.nsteps) lp.status[d.index] = status;
+    } else if (s_end == d.nsteps) {
         // outputs: c, p at T and the QoI
         for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
             lp.c_out[d.field_off + idx] = S.c[idx];
@@ -3126,6 +3134,13 @@ __global__ void __launch_bounds__(1024) henry_residual_kernel(Launch lp, const d
     }
     __syncthreads();
     residual_rows<float, 2, false>(S);
+}
+
+// Before a launch of one workgroup per solve over the same descriptors that
+// takes the solves which reported HENRY_STATUS_SYNC: no steps for the others.
+__global__ void henry_redo_kernel(SolveDesc* descs, int nsolves, const int32_t* status) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < nsolves && status[descs[k].index] != kStatusSync) descs[k].nsteps = 0;
 }
 
 // ------------------------------------------------------------------ random fields

@@ -1306,8 +1306,8 @@ int henry_sample_stats(henry_ctx* ctx, int32_t nsamples, int32_t nvals, const do
     DeviceGuard dg(ctx->device);
     hipStream_t s0 = reinterpret_cast<hipStream_t>(stream);
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((nvals + 7) / 8 * 8), dim3(henry::kStatThreads), 0, s0, x, x_sub, nsamples, nvals, pr, mean_out,
-                           var_out, q_out);
+        hipLaunchKernelGGL(kernel, dim3(nvals), dim3(henry::kStatThreads), 0, s0, x, x_sub, nsamples, nvals, pr,
+                           mean_out, var_out, q_out);
     };
     if (P == 0) launch(henry::sample_moments_kernel);
     else if (P <= 256) launch(henry::sample_stats_kernel<1>);

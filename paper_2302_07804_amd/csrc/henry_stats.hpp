@@ -66,13 +66,14 @@ __device__ inline double block_sum256(double v, double* red) {
     return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// Column of a block: consecutive columns share cache lines, blocks go to the
-// eight XCDs in turn, so every eighth block takes the next column of its
-// XCD's share of them.  -1: past the last.
+// Column of a block (as many blocks as columns: a launch holds fewer than
+// 2^24 blocks of 256 threads): consecutive columns share cache lines, blocks
+// go to the eight XCDs in turn, so every eighth block takes the next column of
+// its XCD's share of them, nvals / 8 columns and one more on the first nvals
+// mod 8 XCDs.
 __device__ inline int stat_column(int nvals) {
-    const int share = (nvals + 7) / 8;
-    const int v = ((int)blockIdx.x & 7) * share + ((int)blockIdx.x >> 3);
-    return ((int)blockIdx.x >> 3) < share && v < nvals ? v : -1;
+    const int x = (int)blockIdx.x & 7, rest = nvals & 7;
+    return x * (nvals >> 3) + min(x, rest) + ((int)blockIdx.x >> 3);
 }
 
 // Sample i of column v (of x - x_sub when given).
@@ -90,7 +91,6 @@ __global__ void __launch_bounds__(kStatThreads) sample_moments_kernel(const doub
                                                                       double*) {
     __shared__ double red[4];
     const int v = stat_column(nvals);
-    if (v < 0) return;
     double s = 0.0;
     for (int i = threadIdx.x; i < nsamples; i += kStatThreads) s += stat_value(x, x_sub, nvals, v, i);
     const double mu = block_sum256(s, red) / nsamples;
@@ -124,7 +124,6 @@ __global__ void __launch_bounds__(kStatThreads) sample_stats_kernel(const double
     __shared__ unsigned long long buf[P];
     __shared__ double red[4];
     const int v = stat_column(nvals), tid = threadIdx.x;
-    if (v < 0) return;
     double a[E];
     double s = 0.0;
 #pragma unroll

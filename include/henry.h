@@ -345,11 +345,12 @@ int henry_first_passage(henry_ctx* ctx, int32_t nsamples, int32_t nrec, int32_t 
                         const double* trace, double threshold, int32_t below, int32_t* t_out, int32_t* hist_out,
                         void* stream);
 
-/* One multigrid level's smoothing on a caller's linear system A x = b, with
- * the device functions the solves run in every V-cycle (the multigrid
- * preconditioning of Sec. 2.3, redesigned: RB Gauss-Seidel for the
+/* One multigrid level's smoothing on a caller's linear system A x = b (the
+ * multigrid preconditioning of Sec. 2.3, redesigned: RB Gauss-Seidel for the
  * pressure, zebra line relaxation for the transport), for checking each on
- * its own.  nx x ny as for a solve; fields [ny][nx] device FP64; x is the
+ * its own: the general device functions, which the solves' cycles take on
+ * their largest levels (on the others they run the same relaxations from
+ * registers or LDS).  nx x ny as for a solve; fields [ny][nx] device FP64; x is the
  * start on entry and the result on return (converted to the inner type of
  * prec and back).
  *   kind 0: `sweeps` red-black Gauss-Seidel sweeps, red cells ((i + j) even)
@@ -402,8 +403,10 @@ int henry_level_smooth(henry_ctx* ctx, int32_t nx, int32_t ny, int32_t kind, int
  * The measuring driver that fills it
  * times candidates on short runs of the caller's own batch (Python
  * binding: paper_2302_07804_amd.autotune).  henry_tune_get returns the
- * workgroup size of a group of one workgroup per solve (of up to 512
- * solves, where it is the built-in one) and the
+ * tuned workgroup size, or else the built-in one of a group of up to 512
+ * solves with one workgroup each (up to 256 adjoints; larger groups take
+ * half of it up to 2048 cells, groups with clusters 512; henry_profile_last
+ * returns what a profiled call took), and the
  * stored cluster and stream (0 / -1 = built-in); cluster and stream may be
  * NULL. */
 int henry_tune_set(henry_ctx* ctx, int32_t nx, int32_t prec, int32_t threads, int32_t cluster, int32_t stream);

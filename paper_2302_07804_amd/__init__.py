@@ -15,8 +15,6 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
 LIB_PATH = os.path.join(_HERE, "libhenry.so")
 _SOURCES = [os.path.join(_HERE, "csrc", f) for f in ("henry_api.hip", "henry_solve512.hip", "henry_mlmc_plan.cpp")]
-_DEPS = [os.path.join(_HERE, "csrc", f) for f in ("henry_device.hpp", "henry_wave.hpp", "henry_mlmc.hpp", "henry_adjoint.hpp")] + \
-    [os.path.join(_ROOT, "include", "henry.h")]
 
 HENRY_OK, HENRY_EINVAL, HENRY_ENOMEM, HENRY_EHIP, HENRY_ENOCONV, HENRY_ENONFINITE = 0, -1, -2, -3, -4, -5
 STATUS_OK, STATUS_NOCONV, STATUS_NONFINITE, STATUS_SYNC = 0, 1, 2, 3
@@ -746,8 +744,9 @@ def henry_tune_set(ctx: Context, nx: int, prec: int, threads: int = 0, cluster: 
 
 
 def henry_tune_get(ctx: Context, nx: int, prec: int):
-    """(threads, cluster, stream) of grids of width nx: the effective
-    workgroup size and the stored cluster and stream (0 / -1: built-in)."""
+    """(threads, cluster, stream) of grids of width nx: the tuned workgroup
+    size, or else the built-in one of a group of up to 512 solves with one
+    workgroup each, and the stored cluster and stream (0 / -1: built-in)."""
     t, k, st = ct.c_int32(), ct.c_int32(), ct.c_int32()
     _chk(lib().henry_tune_get(ctx.handle, nx, prec, ct.byref(t), ct.byref(k), ct.byref(st)), "henry_tune_get")
     return t.value, k.value, st.value
@@ -820,7 +819,8 @@ def autotune(ctx: Context, solves, xi, opts: Opts | None = None, tune_steps: int
          percent that the early steps alone misjudge (L = 4 MLMC batch:
          4 against 8 workgroups per 256x128 solve, 411 and 400 ms).
     Each candidate runs `reps` times and its fastest run counts.  The
-    choices change no result (bitwise).  With cache_path, choices found
+    choices change no result (bitwise; the adjoint's dq_dxi and dq_dq are
+    summed in the order of the workgroup size).  With cache_path, choices found
     there are used as they are and new ones are written back.  Returns
     {(nx, prec): (threads, cluster, stream, {candidate: ms})}."""
     import json

@@ -1,8 +1,15 @@
 // henry_check.hpp -- one multigrid level's smoothing on a caller's linear
 // system: the red-black Gauss-Seidel sweeps of the pressure cycle and the
-// zebra line sweeps of the transport cycle, the same device functions the
-// solves run inside every V-cycle (Sec. 2.3's multigrid-preconditioned
-// iteration, redesigned), exposed so that each can be checked on its own.
+// zebra line sweeps of the transport cycle (Sec. 2.3's
+// multigrid-preconditioned iteration, redesigned), exposed so that each can
+// be checked on its own.  These are the general functions on a level in
+// global memory (rbgs, line_smooth).  The solves' cycles take them on the levels
+// that are too large for one pass of the workgroup or cluster; the others go
+// through forms of the same relaxations that hold the level in registers, in
+// lines or strips, or in one wavefront (rb_down, rb_up, line_down, line_up,
+// strip_up, henry_wave.hpp), with the same bits.  The y-line sweeps and the lines
+// of fewer than 64 cells of line_sweep are reached from here only: the solves
+// run those levels in henry_wave.hpp.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -549,8 +549,6 @@ struct BlockTeam {
     __device__ static void sync() { __syncthreads(); }
 };
 struct WaveTeam {
-    __device__ static int rank() { return threadIdx.x & (kWave - 1); }
-    __device__ static int size() { return kWave; }
     __device__ static void sync() {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -1845,11 +1843,6 @@ __device__ __attribute__((noinline)) void line_sweep_m(Level<T>& v0, int col) {
     Team::sync();
 }
 
-// Rows per lane: x-lines take the fewest rows (at least two) that fit a
-// line in one wavefront; y-lines of 64 to 256 rows take four, so that a
-// wavefront holds two or more neighbouring columns and each of its loads
-// touches half as many (or fewer) cache lines as with one column of strided
-// rows.
 // x-lines of 512 and 1024 cells on the cluster levels (one wavefront per
 // line, MS = 8 or 16 rows per lane).  line_sweep_m gathers a lane's MS
 // consecutive cells, so each of its load instructions touches 32 cache lines
@@ -2282,6 +2275,12 @@ __device__ __attribute__((noinline)) void line_down(Level<T>& v0) {
     Team::sync();
 }
 
+// One colour of lines.  x-lines of 64 to 256 cells take line_sweep_x's four
+// rows per lane, longer ones the fewest that fit a line in one wavefront.
+// y-lines and x-lines of fewer than 64 cells are asked for by
+// henry_level_smooth alone (y-lines of 64 to 256 rows with four rows per lane,
+// so that a wavefront holds two or more neighbouring columns and each of its
+// loads touches half as many, or fewer, cache lines as with one column).
 template <typename T, bool kXLine, bool kTrans = false, class Team = BlockTeam, int AS = 0>
 __device__ void line_sweep(Level<T>& v, int col) {
     const int len = kXLine ? v.nx : v.ny;  // 2 .. 1024, a power of two

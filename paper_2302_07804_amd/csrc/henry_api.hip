@@ -202,6 +202,10 @@ bool use_build512(int prec, int threads, int cluster) {
     return prec == HENRY_PREC_MIXED && cluster > 1 && threads <= 512;
 }
 constexpr int kAdjMaxThreads = 512;
+// Columns from which henry_residual_batch takes henry_residual_kernel<true>, us with
+// <false> and <true>: 64 of 128x64 123 and 110, 16 of 256x128 441 and 364, 8 of
+// 1024x512 8394 and 7263 (four rows ahead cost 1024 of 64x32 263 -> 284).
+constexpr int kResidualWide = 128;
 
 int check_grid(const henry_grid_t& g) {
     if (g.reserved != 0) return HENRY_EINVAL;
@@ -970,8 +974,12 @@ int henry_residual_batch(henry_ctx* ctx, const henry_grid_t* solves, int32_t nso
             l.kl_sigma_logk = kg.sigma_logk;
         }
         hipLaunchKernelGGL(henry::henry_fields_kernel, dim3(l.nsolves), dim3(256), 0, s0, l);
-        hipLaunchKernelGGL(henry::henry_residual_kernel, dim3(l.nsolves), dim3(256), 0, s0, l, p, c, cn, rp_out,
-                           rc_out);
+        if (G.nx >= kResidualWide)
+            hipLaunchKernelGGL(henry::henry_residual_kernel<true>, dim3(l.nsolves), dim3(256), 0, s0, l, p, c, cn, rp_out,
+                               rc_out);
+        else
+            hipLaunchKernelGGL(henry::henry_residual_kernel<false>, dim3(l.nsolves), dim3(256), 0, s0, l, p, c, cn,
+                               rp_out, rc_out);
     }
     if (hipGetLastError() != hipSuccess) return HENRY_EHIP;
     return HENRY_OK;

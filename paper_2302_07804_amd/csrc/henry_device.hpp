@@ -3111,9 +3111,12 @@ __global__ void __launch_bounds__(sizeof(T) == 4 ? HENRY_FP32_THREADS : 512) hen
 // The FP64 residual of one solve's discrete equations at a given state
 // (p, c; previous time level cn): the same residual pass as the solver's,
 // writing R^p and R^c instead of the inner-solve arrays.  One workgroup per
-// solve, after henry_fields_kernel.
-__global__ void __launch_bounds__(1024) henry_residual_kernel(Launch lp, const double* p, const double* c,
-                                                              const double* cn, double* rp, double* rc) {
+// solve, after henry_fields_kernel.  kWide: with the face coefficients formed
+// from K and phi and four rows loaded ahead, for grids of at least
+// kResidualWide columns, where a thread's rows are a long chain of loads.
+template <bool kWide>
+__global__ void __launch_bounds__(kWide ? 256 : 1024)
+    henry_residual_kernel(Launch lp, const double* p, const double* c, const double* cn, double* rp, double* rc) {
     extern __shared__ __align__(256) uint8_t lds_levels[];  // launched with none: no level in LDS
     __shared__ Solve<float> S;
     __shared__ double red[32];
@@ -3135,7 +3138,7 @@ __global__ void __launch_bounds__(1024) henry_residual_kernel(Launch lp, const d
         S.cn[idx] = cn[d.field_off + idx];
     }
     __syncthreads();
-    residual_rows<float, 2, false>(S);
+    residual_rows<float, 2, kWide>(S);
 }
 
 // Before a launch of one workgroup per solve over the same descriptors that

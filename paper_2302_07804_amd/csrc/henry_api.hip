@@ -240,7 +240,10 @@ int check_opts(const henry_opts_t* o) {
 //    81, 114, -, -; 16 of 256x128 295, 207, 142, 100; 64 of them 353, 253,
 //    182, 214.  With other groups beside (when the line was drawn): L = 4
 //    batch with 4 and 8 per 256x128 solve 342 and 264; a L = 3 batch with 1,
-//    2, 4 per 128x64 solve (64 of them) 120, 101, 113.
+//    2, 4 per 128x64 solve (64 of them) 120, 101, 113.  Adjoints likewise
+//    (20 steps of 128x64, 10 of 256x128): 16 of 128x64 88, 66, 59, 60; 128 of
+//    them 107, 87, -, -; 16 of 256x128 224, 140, 96, 72; 64 of them 274, 174,
+//    125, -.
 //  - other grids, which would run after it on the cluster stream: one per
 //    8192 (L = 4 batch with 2 per 128x64 solve too: 385 ms).
 int cluster_size(int nx, int ny, int nsolves, int requested, bool lead, bool alone) {
@@ -279,12 +282,17 @@ int default_threads(int nx, int ny, int prec) {
 
 // The same for a group of more than `many` solves of up to 2048 cells: half
 // of it, so that twice as many solves share a CU (a solve's waits are then
-// others' work).  ms at the built-in size and at half of it: 16x8, 256 solves
-// 4.7 and 4.9, 1024 6.3 and 5.9, 4096 17.1 and 12.4; 32x16, 256 solves 6.9 and
-// 7.1, 1280 17.6 and 11.2; 64x32, 512 solves 23.4 and 23.5, 1024 45.8 and
-// 43.2: 512.  The adjoint kernel's 256 registers let one workgroup of 512
-// threads onto a CU: 256 (32x16, 256 solves 22.1 and 23.4, 1024 53 and 34;
-// 64x32, 512 solves 104 and 78).
+// others' work).  ms of a fifth of the hierarchy's steps at the whole size and
+// at half of it, mixed precision: 16x8, 513 solves 2.93 and 2.90, 2048 5.15
+// and 4.86; 32x16, 513 solves 7.42 and 7.71, 1024 9.27 and 8.84; 64x32, 513
+// solves 45.1 and 29.5, 1024 65.9 and 58.4.  FP64: 16x8, 2048 solves 8.43 and
+// 5.59; 32x16, 513 solves 14.5 and 15.1, 2048 35.5 and 35.9; 64x32, 513 solves
+// 76.0 and 53.8, 2048 235 and 148.  Beside sixteen solves of 128x64 on clusters
+// the same way but for FP64 64x32: 600 solves 81.7 and 78.2, FP64 109 and 113.
+// The adjoint kernel's 256 registers let one workgroup of 512 threads onto a
+// CU: 256.  Ten steps: 16x8, 257 solves 6.97 and 7.28, 1024 8.85 and 8.65;
+// 32x16, 512 solves 12.5 and 13.5, 1024 24.5 and 15.8; 64x32, 257 solves 36.5
+// and 24.6, 1024 84.1 and 60.5 (FP64 50.8 and 34.3, 117 and 86.9).
 constexpr int kManySolves = 512, kManyAdjoints = 256;
 int group_threads(int nx, int ny, int nsolves, int prec, int many) {
     const int t = default_threads(nx, ny, prec);

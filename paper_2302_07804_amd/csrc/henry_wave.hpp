@@ -18,10 +18,10 @@
 // are those of the larger levels (rbgs, line_sweep_m with two rows per lane,
 // restrict_residual -- whose products are rounded before they are added, as
 // a select stands between them there --, prolong_add): bitwise the same results as when these
-// levels ran through them.  FP32, per cycle on one hierarchy (device wall
-// clock), with the generic loops before and here:
-//   32x16 and below  pressure 20.0 -> 6.1 us, transport 23.4 -> 6.7 us
-//   16x8 and below   pressure 10.5 -> 3.0 us, transport 14.7 -> 4.2 us
+// levels ran through them.  FP32, per outer iteration of one solve (phase
+// timers), with the generic loops before and here:
+//   32x16 and below  pressure 22.5 -> 6.8 us, transport 26.1 -> 8.0 us
+//   16x8 and below   pressure 11.4 -> 3.3 us, transport 16.3 -> 5.0 us
 #pragma once
 
 __device__ inline int wave_lane() { return (int)threadIdx.x & (kWave - 1); }
